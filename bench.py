@@ -457,15 +457,15 @@ def main():
                    "variant": args.variant,
                    "polar_phase_ends": phase_ends, "tall_factored_steps": list(factored),
                    "alpha": cfg.alpha, "outer_lr": cfg.outer_lr, "mu": cfg.mu},
-        "roofline": {"bound": "mfma", "kernel": "batched polar products (gemm_%s: Gram, polynomial, update)" %
-                     ("f32_kernel" if args.precision == "fp32" else
-                      "bf16_kernel, gemm_bf16_big_kernel" if args.precision == "bf16x6" else
-                      "bf16_kernel, gemm_bf16_big16_kernel"),
+        "roofline": {"bound": "mfma", "kernel": "batched polar products (%s: Gram, polynomial, update)" %
+                     ("gemm_f32_kernel" if args.precision == "fp32" else
+                      "gemm_bf16_kernel, gemm_bf16_big_kernel" if args.precision == "bf16x6" else
+                      "plane_gemm_kernel"),
                      "achieved": round(gemm_tfs, 3), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(gemm_tfs / peak, 4),
                      "work": "the method's products as fp32 flops (symmetric Gram n(n+1)m, polynomial "
                              "n(n+1)n, update 2mn^2 per polar step; a factored step of a tall matrix: "
-                             "A M 2n^3, M B and M P n(n+1)n each) over the time some product runs",
+                             "A M 2n^3 (its symmetric half is computed), M B and M P n(n+1)n each) over the time some product runs",
                      "traffic": mt["gemm_bytes_per_step"] if measured else None,
                      "traffic_unit": "HBM bytes per step over all product launches",
                      "traffic_source": ("stored: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on these sources "

@@ -11,7 +11,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libisoloco.so")
-SOURCES = [os.path.join(PKG, "csrc", f) for f in ("isoloco_host.cpp", "isoloco_kernels.hip")]
+SOURCES = [os.path.join(PKG, "csrc", f) for f in ("isoloco_host.cpp", "isoloco_kernels.hip", "isoloco_products.hip")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",

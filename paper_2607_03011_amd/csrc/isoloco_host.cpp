@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -123,6 +124,12 @@ int step_arith(int precision, int k, int product) {
     default: return (product == kProdUpdate && k < kX6Steps) ? kArithBf16x5 : kArithBf16x3;
   }
 }
+// Matrices with more rows than this keep the products on float32 operands (the
+// plane kernels address a tile's rows with 32-bit offsets).
+constexpr int64_t kPlaneMaxRows = ((int64_t)1 << 21) - kPlaneBlock;
+// The array of third parts takes 4 bytes per element of the corrected matrices
+// (less what the factored steps then share): up to this size.
+constexpr int64_t kThirdMaxBytes = (int64_t)1 << 31;
 constexpr double kSafety = 1.02;
 // The fast variant's iteration: the quintic of the Muon optimizer's reference
 // implementation, p(x) = 3.4445 x - 4.7750 x^3 + 2.0315 x^5, five times.
@@ -338,7 +345,20 @@ struct TaskListHost {
   int rem_cnt[2] = {0, 0};
 };
 
+struct PlaneListHost {
+  std::vector<Task> tasks;
+  int tile = kTileM;
+};
+
 struct isoloco_plan_s {
+  bool planes = false;  // the split-bf16 products run on pre-split operands
+  bool third = false;   // ... the bf16x5 updates' too, with third parts in an array of their own
+  size_t off_third = 0;
+  int64_t n2d_tall = 0;  // elements of the tall matrices in one Delta / X buffer (they come first)
+  PlaneListHost gram_pl, poly_pl, update_pl, cont_gram_pl, cont_update_pl;
+  PlaneListHost gram_plc[kSchedClasses], poly_plc[kSchedClasses], update_plc[kSchedClasses];
+  // every task list above with the offset of its device copy
+  std::vector<std::pair<const PlaneListHost*, size_t>> pl_off;
   std::vector<isoloco_tensor> layout;
   int64_t n_elems = 0;
   int K = 0;
@@ -449,10 +469,86 @@ void build_phases(const isoloco_options& o, const float (&bound)[3], std::vector
   }
 }
 
+// Side of the tiles of a plane product list: see plan_plane_lists.
+constexpr int kTileSide[3] = {64, 128, 256};
+
+// The work lists of the plane products: per list one tile shape, every matrix
+// covered by it (tiles may reach past a matrix).
+void plan_plane_lists(isoloco_plan_s* p) {
+  auto build = [&](const std::vector<MatInfo>& mats, int cls, PlaneListHost& G, PlaneListHost* P, PlaneListHost& U) {
+    std::vector<int> order;
+    for (size_t i = 0; i < mats.size(); ++i)
+      if (cls < 0 || mats[i].sched == cls) order.push_back((int)i);
+    // The largest tiles that still fill the chip (each halves the operand
+    // traffic of the next smaller, but a launch of too few leaves CUs idle) and
+    // do not compute much more than the next smaller ones.  Measured (us per
+    // launch, 64 / 128 / 256): Gram of 8 matrices 768^2 (624 / 168 / 48 tiles)
+    // 27 / 25 / -, of 48 (1008 / 288 of 128 / 256) - / 83 / 119, step with 96 of
+    // 1024^2 (3456 / 960) 49.2 / 48.6 ms; update of 48 of 768^2 (1728 / 432)
+    // - / 137 / 130, of one 4096^2 (1024 / 256) - / 354 / 309.
+    auto choose = [&](bool update) {
+      int64_t tiles[3];
+      for (int t : {kTileS, kTileM, kTileL}) {
+        const int64_t S = kTileSide[t];
+        tiles[t] = 0;
+        for (int i : order) {
+          const int64_t TN = (mats[i].np + S - 1) / S, TM = (mats[i].mp + S - 1) / S;
+          tiles[t] += update ? TM * TN : TN * (TN + 1) / 2 * mats[i].ksplit;
+        }
+      }
+      // (tiles on the diagonal compute more than they must: 1.25 allows for them)
+      if (tiles[kTileL] >= (update ? 256 : 512) && 4 * tiles[kTileL] <= (update ? 1.1 : 1.25) * tiles[kTileM])
+        return (int)kTileL;
+      if (tiles[kTileM] >= 160 && 4 * tiles[kTileM] <= 1.6 * tiles[kTileS]) return (int)kTileM;
+      return (int)kTileS;
+    };
+    G.tile = choose(false);
+    U.tile = choose(true);
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int a, int b) { return (int64_t)mats[a].kchunk > (int64_t)mats[b].kchunk; });
+    const int S = kTileSide[G.tile], SU = kTileSide[U.tile];
+    for (int mi : order)
+      for (int ks = 0; ks < mats[mi].ksplit; ++ks)
+        for (int a = 0; a < (mats[mi].np + S - 1) / S; ++a)
+          for (int b = a; b < (mats[mi].np + S - 1) / S; ++b) G.tasks.push_back(Task{mi, a, b, ks});
+    G.tasks = xcd_order(mats, G.tasks, true);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return mats[a].n > mats[b].n; });
+    for (int mi : order)
+      for (int a = 0; a < (mats[mi].mp + SU - 1) / SU; ++a)
+        for (int b = 0; b < (mats[mi].np + SU - 1) / SU; ++b) U.tasks.push_back(Task{mi, a, b, 0});
+    U.tasks = xcd_order(mats, U.tasks, false);
+    if (!P) return;
+    // (the polynomial reads the blocks that the Gram's tiles left: one shape for both)
+    P->tile = G.tile;
+    for (int mi : order)
+      for (int a = 0; a < (mats[mi].np + S - 1) / S; ++a)
+        for (int b = a; b < (mats[mi].np + S - 1) / S; ++b) P->tasks.push_back(Task{mi, a, b, 0});
+    P->tasks = xcd_order(mats, P->tasks, false);
+  };
+  build(p->mats, -1, p->gram_pl, &p->poly_pl, p->update_pl);
+  for (int c = 0; c < kSchedClasses; ++c)
+    build(p->mats, c, p->gram_plc[c], &p->poly_plc[c], p->update_plc[c]);
+  build(p->cmats, -1, p->cont_gram_pl, nullptr, p->cont_update_pl);
+  // (the factored steps' polynomials run on the tall class's list)
+}
+
 void plan_matrices(isoloco_plan_s* p) {
   const int V = p->dtype == ISOLOCO_BF16 ? 8 : 4;
   int64_t ws = 0, sq = 0, part = 0;
   p->mat_of_tensor.assign(p->layout.size(), -1);
+  auto padded = [&](int64_t v) { return p->planes ? (v + kPlaneBlock - 1) / kPlaneBlock * kPlaneBlock : v; };
+  // places in the Delta / X buffers, the tall matrices' first
+  std::vector<int64_t> ws_of(p->layout.size(), 0);
+  for (int pass = 0; pass < 2; ++pass) {
+    for (size_t t = 0; t < p->layout.size(); ++t) {
+      const isoloco_tensor& T = p->layout[t];
+      const int64_t m = std::max(T.rows, T.cols), n = std::min(T.rows, T.cols);
+      if (T.kind != ISOLOCO_KIND_ISO || (m >= 2 * n) != (pass == 0)) continue;
+      ws_of[t] = ws;
+      ws += (padded(m) * padded(n) + 63) / 64 * 64;
+    }
+    if (pass == 0) p->n2d_tall = ws;
+  }
   // corrected matrices and their chunks first
   for (size_t t = 0; t < p->layout.size(); ++t) {
     const isoloco_tensor& T = p->layout[t];
@@ -471,8 +567,11 @@ void plan_matrices(isoloco_plan_s* p) {
     mi.m = (int32_t)std::max(T.rows, T.cols);
     mi.n = (int32_t)std::min(T.rows, T.cols);
     mi.src_off = T.offset;
-    mi.ws_off = ws;
+    mi.ws_off = ws_of[t];
     mi.vec = (mi.m % 4 == 0 && mi.n % 4 == 0) ? 1 : 0;
+    mi.mp = (int32_t)padded(mi.m);
+    mi.np = (int32_t)padded(mi.n);
+    const int64_t nn = (int64_t)mi.np * mi.np;
     mi.tensor = (int32_t)t;
     mi.sched = mi.m >= 2 * (int64_t)mi.n ? kSchedTall : kSchedSquare;
     if (mi.sched == kSchedSquare) p->sq_tiles += (int64_t)((mi.m + 255) / 256) * ((mi.n + 255) / 256);
@@ -486,7 +585,7 @@ void plan_matrices(isoloco_plan_s* p) {
       ks = (int)std::min<int64_t>(kMaxKSplit, (mi.m + 1023) / 1024);
     // the slices of one matrix stay under 2 GiB (the Gram epilogue addresses
     // them with 32-bit buffer offsets)
-    while (ks > 1 && 4 * (int64_t)ks * mi.n * mi.n >= ((int64_t)1 << 31)) --ks;
+    while (ks > 1 && 4 * (int64_t)ks * nn >= ((int64_t)1 << 31)) --ks;
     int64_t kchunk = (mi.m + ks - 1) / ks;
     kchunk = (kchunk + 31) / 32 * 32;  // whole K slabs of both product kernels
     ks = (int)((mi.m + kchunk - 1) / kchunk);
@@ -496,13 +595,13 @@ void plan_matrices(isoloco_plan_s* p) {
     mi.cnt_off = -1;
     if (ks > 1) {
       mi.part_off = part;
-      part += (int64_t)ks * mi.n * mi.n;
+      part += (int64_t)ks * nn;
       part = (part + 63) / 64 * 64;
       mi.cnt_off = (int32_t)p->n_cnt;
-      p->n_cnt += gram_tiles(mi.n);
+      p->n_cnt += p->planes ? sym_tiles(mi.n, 64) : gram_tiles(mi.n);
     }
     mi.norm_off = (int32_t)p->n_norm;
-    p->n_norm += gram_tiles(mi.n);
+    p->n_norm += p->planes ? sym_tiles(mi.n, 64) : gram_tiles(mi.n);
     const int64_t cnt = (int64_t)mi.m * mi.n;
     mi.chunk_begin = (int32_t)p->chunks.size();
     if (tiled) {
@@ -513,7 +612,7 @@ void plan_matrices(isoloco_plan_s* p) {
           c.rows = (int32_t)std::min<int64_t>(kTileRows, R - r0);
           c.cols = (int32_t)std::min<int64_t>(kTileCols, C - c0);
           c.src = T.offset + r0 * C + c0;
-          c.ws = ws + c0 * R + r0;
+          c.ws = mi.ws_off + c0 * R + r0;
           c.count = c.rows * c.cols;
           c.mat = (int32_t)p->mats.size();
           c.src_ld = (int32_t)C;
@@ -525,7 +624,7 @@ void plan_matrices(isoloco_plan_s* p) {
       for (int64_t s = 0; s < cnt; s += kChunk) {
         Chunk c{};
         c.src = T.offset + s;
-        c.ws = ws + s;
+        c.ws = mi.ws_off + s;
         c.count = (int32_t)std::min<int64_t>(kChunk, cnt - s);
         c.mat = (int32_t)p->mats.size();
         c.vec = (T.offset % V == 0) ? 1 : 0;
@@ -535,7 +634,6 @@ void plan_matrices(isoloco_plan_s* p) {
     mi.chunk_end = (int32_t)p->chunks.size();
     p->mat_of_tensor[t] = (int)p->mats.size();
     p->mats.push_back(mi);
-    ws += (cnt + 63) / 64 * 64;
   }
   // the n x n buffers of the tall matrices first: the factored steps' own
   // buffers then cover [0, nsq_tall) only
@@ -543,7 +641,7 @@ void plan_matrices(isoloco_plan_s* p) {
     for (MatInfo& mi : p->mats)
       if ((mi.sched == kSchedTall) == (pass == 0)) {
         mi.sq_off = sq;
-        sq += ((int64_t)mi.n * mi.n + 63) / 64 * 64;
+        sq += ((int64_t)mi.np * mi.np + 63) / 64 * 64;
       }
     if (pass == 0) p->nsq_tall = sq;
   }
@@ -553,6 +651,7 @@ void plan_matrices(isoloco_plan_s* p) {
     if (mi.sched != kSchedTall) continue;
     MatInfo c = mi;
     c.m = mi.n;
+    c.mp = mi.np;
     c.ws_off = mi.sq_off;
     c.ksplit = 1;
     c.kchunk = (mi.n + 31) / 32 * 32;
@@ -583,6 +682,10 @@ void plan_matrices(isoloco_plan_s* p) {
   p->nsq = sq;
   p->npart = part;
 
+  if (p->planes) {
+    plan_plane_lists(p);
+    return;
+  }
   // Work lists, longest tasks first, each in two segments (interior tiles,
   // ragged tiles), each segment reordered for the XCD round robin of the
   // dispatcher.  Next to this cover by 128 x 128 tiles, the split-bf16
@@ -694,6 +797,20 @@ void plan_workspace(isoloco_plan_s* p) {
   p->off_cnt = take((size_t)p->n_cnt * sizeof(int));
   p->off_mcnt = take(p->mats.size() * sizeof(int));
   p->off_coef = take(p->coef.size() * sizeof(float));
+  if (p->planes) {
+    p->pl_off.clear();
+    auto list = [&](const PlaneListHost& l) { p->pl_off.push_back({&l, take(l.tasks.size() * sizeof(Task))}); };
+    list(p->gram_pl);
+    list(p->poly_pl);
+    list(p->update_pl);
+    list(p->cont_gram_pl);
+    list(p->cont_update_pl);
+    for (int c = 0; c < kSchedClasses; ++c) {
+      list(p->gram_plc[c]);
+      list(p->poly_plc[c]);
+      list(p->update_plc[c]);
+    }
+  }
   p->off_delta = take((size_t)p->n2d * sizeof(float));
   p->off_x0 = take((size_t)p->n2d * sizeof(float));
   p->off_x1 = take((size_t)p->n2d * sizeof(float));
@@ -707,9 +824,25 @@ void plan_workspace(isoloco_plan_s* p) {
   p->off_cm = take(cont ? p->cmats.size() * sizeof(MatInfo) : 0);
   p->off_cgt = take(cont ? p->cont_gram.tasks.size() * sizeof(Task) : 0);
   p->off_cut = take(cont ? p->cont_update.tasks.size() * sizeof(Task) : 0);
-  p->off_cx = take(cont ? (size_t)p->nsq_tall * sizeof(float) : 0);
-  p->off_cy = take(cont ? (size_t)p->nsq_tall * sizeof(float) : 0);
+  // The third parts are last read by step kX6Steps - 1's update: the factored
+  // steps, which start later, take the tall matrices' part of that array where
+  // it holds their two buffers.
+  p->off_third = take(p->third ? (size_t)p->n2d * sizeof(float) : 0);
+  if (cont && p->third && p->cont_from >= kX6Steps && p->n2d_tall >= 2 * p->nsq_tall) {
+    p->off_cx = p->off_third;
+    p->off_cy = p->off_third + (size_t)p->nsq_tall * sizeof(float);
+  } else {
+    p->off_cx = take(cont ? (size_t)p->nsq_tall * sizeof(float) : 0);
+    p->off_cy = take(cont ? (size_t)p->nsq_tall * sizeof(float) : 0);
+  }
   p->total = o;
+}
+
+PlaneList dev_plane_list(const isoloco_plan_s* p, const char* w, const PlaneListHost& L) {
+  PlaneList d{};
+  for (const auto& e : p->pl_off)
+    if (e.first == &L) d = {reinterpret_cast<const Task*>(w + e.second), (int)L.tasks.size(), L.tile};
+  return d;
 }
 
 TaskList dev_list(const char* w, const TaskListHost& L, size_t off) {
@@ -732,6 +865,9 @@ DevTables class_tables(const isoloco_plan_s* p, const char* w, const DevTables& 
   d.gram_list = dev_list(w, p->gram_cls[c], p->off_gtc[c]);
   d.poly_list = dev_list(w, p->poly_cls[c], p->off_ptc[c]);
   d.update_list = dev_list(w, p->update_cls[c], p->off_utc[c]);
+  d.gram_pl = dev_plane_list(p, w, p->gram_plc[c]);
+  d.poly_pl = dev_plane_list(p, w, p->poly_plc[c]);
+  d.update_pl = dev_plane_list(p, w, p->update_plc[c]);
   d.chunk_idx = reinterpret_cast<const int*>(w + p->off_cic[c]);
   d.n_chunk_idx = (int)p->chunk_cls[c].size();
   d.cls = c;
@@ -747,6 +883,9 @@ DevTables cont_tables(const isoloco_plan_s* p, const char* w, const DevTables& t
   d.gram_list = dev_list(w, p->cont_gram, p->off_cgt);
   d.update_list = dev_list(w, p->cont_update, p->off_cut);
   d.poly_list = TaskList{};
+  d.gram_pl = dev_plane_list(p, w, p->cont_gram_pl);
+  d.update_pl = dev_plane_list(p, w, p->cont_update_pl);
+  d.poly_pl = PlaneList{};
   d.n_mat = (int)p->cmats.size();
   return d;
 }
@@ -759,6 +898,11 @@ DevTables dev_tables(const isoloco_plan_s* p, char* w) {
   t.gram_list = dev_list(w, p->gram_list, p->off_gt);
   t.poly_list = dev_list(w, p->poly_list, p->off_pt);
   t.update_list = dev_list(w, p->update_list, p->off_ut);
+  t.planes = p->planes ? 1 : 0;
+  t.gram_pl = dev_plane_list(p, w, p->gram_pl);
+  t.poly_pl = dev_plane_list(p, w, p->poly_pl);
+  t.update_pl = dev_plane_list(p, w, p->update_pl);
+  t.third = p->third ? reinterpret_cast<uint16_t*>(w + p->off_third) : nullptr;
   t.scalars = reinterpret_cast<MatScalars*>(w + p->off_sc);
   t.part_sq = reinterpret_cast<double*>(w + p->off_psq);
   t.part_tr = reinterpret_cast<double*>(w + p->off_ptr);
@@ -799,6 +943,8 @@ hipError_t upload_tables(const isoloco_plan_s* plan, char* w) {
       (e = up(plan->off_ut, plan->update_list.tasks.data(), plan->update_list.tasks.size() * sizeof(Task))) != hipSuccess ||
       (e = up(plan->off_coef, plan->coef.data(), plan->coef.size() * sizeof(float))) != hipSuccess)
     return e;
+  for (const auto& l : plan->pl_off)
+    if ((e = up(l.second, l.first->tasks.data(), l.first->tasks.size() * sizeof(Task))) != hipSuccess) return e;
   if (plan->cont_to > 0 &&
       ((e = up(plan->off_cm, plan->cmats.data(), plan->cmats.size() * sizeof(MatInfo))) != hipSuccess ||
        (e = up(plan->off_cgt, plan->cont_gram.tasks.data(), plan->cont_gram.tasks.size() * sizeof(Task))) !=
@@ -828,12 +974,88 @@ hipError_t upload_tables(const isoloco_plan_s* plan, char* w) {
   return hipStreamSynchronize(nullptr);
 }
 
+// Arithmetic of a plan's products: without planes the split modes run bf16x6
+// (every product at least as accurate as the mode asks for).
+int polar_precision(const isoloco_plan_s* p) {
+  return p->planes || p->opts.precision == ISOLOCO_PREC_FP32 ? p->opts.precision : ISOLOCO_PREC_BF16X6;
+}
+
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
   return x < y + nb && y < x + na;
 }
 
 }  // namespace
+
+// A plan for validated arguments; planes: the split-bf16 products on
+// pre-split operands.
+static isoloco_plan_s* build_plan(const isoloco_tensor* layout, int32_t n_tensors, int64_t n_elems, int32_t K,
+                                  isoloco_dtype worker_dtype, isoloco_options o, bool planes) {
+  std::unique_ptr<isoloco_plan_s> owner(new isoloco_plan_s());
+  isoloco_plan_s* p = owner.get();
+  p->uid = g_next_uid.fetch_add(1);
+  p->layout.assign(layout, layout + n_tensors);
+  p->n_elems = n_elems;
+  p->K = K;
+  p->dtype = worker_dtype;
+  p->planes = planes;
+  plan_matrices(p);
+  if (o.streams == 0) {
+    // Two streams fill each other's launch gaps and partial last waves,
+    // which matter while launches are short; for large matrices the
+    // concurrent products rather compete for the caches (paired
+    // measurements: 109.5M parameters 2% faster, 341M 1%, 888M 4% slower).
+    int64_t n2d = 0;
+    for (const MatInfo& mi : p->mats) n2d += (int64_t)mi.m * mi.n;
+    o.streams = n2d <= kTwoStreamMaxElems ? 2 : 1;
+  }
+  p->opts = o;
+  for (int c = 0; c < kSchedClasses; ++c)
+    build_phases(o, c == kSchedTall ? o.phase_tall : o.phase_square, p->sched[c], p->phase_end[c],
+                 p->phase_bound[c]);
+  p->n_steps = 0;
+  for (int c = 0; c < kSchedClasses; ++c) p->n_steps = std::max(p->n_steps, p->phase_end[c].back());
+  // The tall class's factored steps: from the first step s whose image of
+  // the first phase's bound reaches kFactorMinBound to the end of that
+  // phase.  X_s and the phase's result sit in different X buffers (the
+  // result of step k goes to x[k & 1]), so s and the phase end differ in
+  // parity (s moves on by one if not), and at least two steps remain after
+  // s, else nothing is saved.
+  if (o.factored != 2 && o.orth == ISOLOCO_ORTH_POLAR && !p->cmats.empty()) {
+    const std::vector<double>& sc = p->sched[kSchedTall];
+    const int e1 = p->phase_end[kSchedTall][0];
+    double l = p->phase_bound[kSchedTall][0];
+    for (int k = 1; k <= e1 - 3; ++k) {
+      l = peval(&sc[3 * (k - 1)], l);
+      // (on planes A M takes no third part of A: not before the bf16x5 steps end)
+      if (p->planes && o.precision == ISOLOCO_PREC_MIXED && k + 1 < kX6Steps) continue;
+      if (l >= kFactorMinBound && (e1 - k) % 2 == 1) {
+        p->cont_from = k;
+        p->cont_to = e1;
+        break;
+      }
+    }
+  }
+  p->coef.assign((size_t)kSchedClasses * p->n_steps * 3, 0.f);
+  for (int c = 0; c < kSchedClasses; ++c)
+    for (int k = 0; k < p->n_steps; ++k) {
+      const int kk = std::min(k, (int)p->sched[c].size() / 3 - 1);
+      for (int q = 0; q < 3; ++q) p->coef[((size_t)c * p->n_steps + k) * 3 + q] = (float)p->sched[c][3 * kk + q];
+    }
+  plan_workspace(p);
+  if (p->planes && o.precision == ISOLOCO_PREC_MIXED) {
+    // The third parts' array where it stays small, and where the plan would
+    // not lose its place in the static workspace by it.
+    const size_t plain = p->total;
+    p->third = 4 * p->n2d <= kThirdMaxBytes;
+    plan_workspace(p);
+    if (p->third && p->total > ISOLOCO_STATIC_WORKSPACE_BYTES && plain <= ISOLOCO_STATIC_WORKSPACE_BYTES) {
+      p->third = false;
+      plan_workspace(p);
+    }
+  }
+  return owner.release();
+}
 
 extern "C" {
 
@@ -912,56 +1134,23 @@ isoloco_status isoloco_plan(const isoloco_tensor* layout, int32_t n_tensors, int
     if (spans[i].first < spans[i - 1].second)
       return fail(ISOLOCO_ERR_LAYOUT, "tensors overlap at element %lld", (long long)spans[i].first);
 
-  isoloco_plan_s* p = new (std::nothrow) isoloco_plan_s();
-  if (!p) return fail(ISOLOCO_ERR_INVALID_ARG, "out of host memory");
+  isoloco_plan_s* p = nullptr;
   try {
-    p->uid = g_next_uid.fetch_add(1);
-    p->layout.assign(layout, layout + n_tensors);
-    p->n_elems = n_elems;
-    p->K = K;
-    p->dtype = worker_dtype;
-    plan_matrices(p);
-    if (o.streams == 0) {
-      // Two streams fill each other's launch gaps and partial last waves,
-      // which matter while launches are short; for large matrices the
-      // concurrent products rather compete for the caches (paired
-      // measurements: 109.5M parameters 2% faster, 341M 1%, 888M 4% slower).
-      int64_t n2d = 0;
-      for (const MatInfo& mi : p->mats) n2d += (int64_t)mi.m * mi.n;
-      o.streams = n2d <= kTwoStreamMaxElems ? 2 : 1;
-    }
-    p->opts = o;
-    for (int c = 0; c < kSchedClasses; ++c)
-      build_phases(o, c == kSchedTall ? o.phase_tall : o.phase_square, p->sched[c], p->phase_end[c],
-                   p->phase_bound[c]);
-    p->n_steps = 0;
-    for (int c = 0; c < kSchedClasses; ++c) p->n_steps = std::max(p->n_steps, p->phase_end[c].back());
-    // The tall class's factored steps: from the first step s whose image of
-    // the first phase's bound reaches kFactorMinBound to the end of that
-    // phase.  X_s and the phase's result sit in different X buffers (the
-    // result of step k goes to x[k & 1]), so s and the phase end differ in
-    // parity (s moves on by one if not), and at least two steps remain after
-    // s, else nothing is saved.
-    if (o.factored != 2 && o.orth == ISOLOCO_ORTH_POLAR && !p->cmats.empty()) {
-      const std::vector<double>& sc = p->sched[kSchedTall];
-      const int e1 = p->phase_end[kSchedTall][0];
-      double l = p->phase_bound[kSchedTall][0];
-      for (int k = 1; k <= e1 - 3; ++k) {
-        l = peval(&sc[3 * (k - 1)], l);
-        if (l >= kFactorMinBound && (e1 - k) % 2 == 1) {
-          p->cont_from = k;
-          p->cont_to = e1;
-          break;
-        }
+    bool planes = o.precision == ISOLOCO_PREC_MIXED || o.precision == ISOLOCO_PREC_BF16X3;
+    int64_t iso = 0;
+    for (int32_t i = 0; i < n_tensors; ++i)
+      if (layout[i].kind == ISOLOCO_KIND_ISO) {
+        iso += layout[i].rows * layout[i].cols;
+        if (std::max(layout[i].rows, layout[i].cols) > kPlaneMaxRows) planes = false;
       }
+    p = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
+    // The padding of many small matrices can take a plan past the static
+    // workspace that would fit without it: such a plan keeps float32 operands.
+    if (planes && p->total > ISOLOCO_STATIC_WORKSPACE_BYTES && 12 * iso <= (int64_t)ISOLOCO_STATIC_WORKSPACE_BYTES) {
+      isoloco_plan_s* q = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, false);
+      if (q->total <= ISOLOCO_STATIC_WORKSPACE_BYTES) std::swap(p, q);
+      delete q;
     }
-    p->coef.assign((size_t)kSchedClasses * p->n_steps * 3, 0.f);
-    for (int c = 0; c < kSchedClasses; ++c)
-      for (int k = 0; k < p->n_steps; ++k) {
-        const int kk = std::min(k, (int)p->sched[c].size() / 3 - 1);
-        for (int q = 0; q < 3; ++q) p->coef[((size_t)c * p->n_steps + k) * 3 + q] = (float)p->sched[c][3 * kk + q];
-      }
-    plan_workspace(p);
   } catch (...) {
     delete p;
     return fail(ISOLOCO_ERR_INVALID_ARG, "out of host memory while planning");
@@ -1098,6 +1287,7 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
     const bool two = use_side && plan->opts.streams == 2 && plan->side && n_cls[0] > 0 && n_cls[1] > 0;
     plan->last_streams = two ? 2 : 1;
     const char* what = "";
+    const int prec = polar_precision(plan);
     // The polar iteration of the matrices of class cls (-1: every matrix) on
     // stream s, from the scalars fro_kernel set (tt.scalars; the matrices are
     // in tt.delta); the factor of matrix m ends in tt.x[scalars[m].qbuf].
@@ -1146,6 +1336,18 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
         ps.norm.mode = mode;
         return gram(ps);
       };
+      // (plane layout) is X_k float32?  Delta, the iterates whose updates take a
+      // third part (unless those have an array), and those at a phase end of a
+      // class in these launches, where X_k may be the factor; planes otherwise
+      auto is_x5 = [&](int k) { return step_arith(prec, k, kProdUpdate) == kArithBf16x5; };
+      auto is_float = [&](int k) {
+        if (k == 0 || (is_x5(k) && !plan->third)) return true;
+        for (int c = 0; c < kSchedClasses; ++c)
+          if (cls < 0 || c == cls)
+            for (int end : plan->phase_end[c])
+              if (end == k) return true;
+        return false;
+      };
       // Steps cont_from .. cont_to - 1 of the tall matrices on n x n factors,
       // after step s = cont_from's Gram A = X_s^T X_s (in tt.gram, left there
       // throughout): M = p_s(A), then for each step k B = A M, A_k = M B,
@@ -1154,7 +1356,6 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
       // buffers of the tall matrices, B and P the polynomial buffer.  The
       // n x n launches run every tall matrix (only_active = 0: none has
       // stopped before its first phase end).
-      const int prec = plan->opts.precision;
       auto factored_steps = [&](const PolarStep& ps) -> hipError_t {
         hipError_t q;
         const DevTables tc = cont_tables(plan, ws, tt);
@@ -1182,7 +1383,15 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
           pp.step = k;
           pp.only_active = 1;
           pp.arith = step_arith(prec, k, kProdPoly);
-          if ((q = timed_on(s, kPhUpdate, [&] { return launch_gemm(ta, 2, pa, s); })) != hipSuccess ||
+          // (plane layout) A and M commute: B is symmetric too
+          PolarStep ps2 = pb;
+          ps2.xin = tt.gram;
+          ps2.bin = cur;
+          DevTables t2 = tc;
+          t2.gram = tt.poly;
+          if ((q = timed_on(s, plan->planes ? kPhGram : kPhUpdate, [&] {
+                return plan->planes ? launch_gemm(t2, 0, ps2, s) : launch_gemm(ta, 2, pa, s);
+              })) != hipSuccess ||
               (q = timed_on(s, kPhGram, [&] { return launch_gemm(tb, 0, pb, s); })) != hipSuccess ||
               (q = timed_on(s, kPhPoly, [&] { return launch_gemm(tp, 1, pp, s); })) != hipSuccess ||
               (q = timed_on(s, kPhGram, [&] { return launch_gemm(tb, 0, pb, s); })) != hipSuccess)
@@ -1197,6 +1406,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
         pq.step = plan->cont_to - 1;
         pq.only_active = 1;
         pq.arith = step_arith(prec, plan->cont_to - 1, kProdUpdate);
+        pq.x_float = is_float(plan->cont_from);
+        pq.out_float = true;
         return timed_on(s, kPhUpdate, [&] { return launch_gemm(tq, 2, pq, s); });
       };
       const bool factored =
@@ -1210,7 +1421,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
         ps.step = k;
         ps.first = (k == 0);
         ps.only_active = 1;
-        ps.arith = step_arith(plan->opts.precision, k, kProdGram);
+        ps.arith = step_arith(prec, k, kProdGram);
+        ps.x_float = is_float(k);
         what = "polar step launch";
         // (the fast variant keeps X0 = Delta / ||Delta||_F: no Gram-norm scaling)
         if (!have_gram && (r = (k == 0 && !ns5) ? gram_norm(ps, kNormFirst) : gram(ps)) != hipSuccess) return r;
@@ -1220,8 +1432,10 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
           xin = tt.x[k & 1];
         } else {
           PolarStep pp = ps, pu = ps;
-          pp.arith = step_arith(plan->opts.precision, k, kProdPoly);
-          pu.arith = step_arith(plan->opts.precision, k, kProdUpdate);
+          pp.arith = step_arith(prec, k, kProdPoly);
+          pu.arith = step_arith(prec, k, kProdUpdate);
+          pu.out_float = is_float(k + 1);
+          pu.third = plan->planes && plan->third && !pu.out_float && is_x5(k + 1);
           if ((r = timed_on(s, kPhPoly, [&] { return launch_gemm(tt, 1, pp, s); })) != hipSuccess ||
               (r = timed_on(s, kPhUpdate, [&] { return launch_gemm(tt, 2, pu, s); })) != hipSuccess)
             return r;
@@ -1246,7 +1460,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
           PolarStep pc{};
           pc.xin = xin;
           pc.only_active = 1;
-          pc.arith = step_arith(plan->opts.precision, k + 1, kProdGram);
+          pc.arith = step_arith(prec, k + 1, kProdGram);
+          pc.x_float = true;
           if ((r = gram_norm(pc, kNormPhase)) != hipSuccess) return r;
           have_gram = true;
         } else {
@@ -1269,7 +1484,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
         PolarStep pc{};
         pc.xin = xin;
         pc.only_active = 1;
-        pc.arith = step_arith(plan->opts.precision, Sx, kProdGram);
+        pc.arith = step_arith(prec, Sx, kProdGram);
+        pc.x_float = true;
         what = "check launch";
         if ((r = gram_norm(pc, kNormPhase)) != hipSuccess) return r;
       }
@@ -1382,7 +1598,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
       pc.xin = t.x[0];
       pc.xin_alt = t.x[1];
       pc.bin = t.delta;
-      pc.arith = step_arith(plan->opts.precision, S, kProdGram);
+      pc.x_float = true;
+      pc.arith = step_arith(prec, S, kProdGram);
       pc.norm_mode = -1;
       hipError_t r = timed(kPhGram, [&] { return launch_gemm(t2, 0, pc, st); });
       if (r != hipSuccess) return hip_fail(r, "clip product launch");
@@ -1391,7 +1608,8 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
       PolarStep pu{};
       pu.xin = t.x2;
       pu.xout = t.x[0];
-      pu.arith = step_arith(plan->opts.precision, S, kProdUpdate);
+      pu.x_float = pu.out_float = true;
+      pu.arith = step_arith(prec, S, kProdUpdate);
       if ((e = timed(kPhUpdate, [&] { return launch_gemm(t3, 2, pu, st); })) != hipSuccess)
         return hip_fail(e, "clip product launch");
       if ((e = timed(kPhOther, [&] { return launch_clip_compose(t, a, st); })) != hipSuccess)

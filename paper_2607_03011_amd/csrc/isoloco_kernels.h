@@ -6,15 +6,6 @@
 
 namespace isoloco {
 
-// A task list of 128 x 128 tiles in segments: interior tiles (segment 0, both
-// storage orders, the kernel picking the loaders per task; in the update
-// lists the column-major ones go to segment 1 instead) and tiles that touch a
-// ragged edge (segment 2, bounds-checked kernel).  In
-// the update lists the same array also holds the cover the split-bf16
-// kernels use: interior 256 x 256 tiles (big segments 0 and 1, split by
-// storage order like the 128 x 128 ones) plus, in segments as above, the
-// 128 x 128 tiles they leave uncovered; the Gram and polynomial lists have no
-// 256 x 256 tiles (rem = seg).
 // A product's work list: the 128 x 128 cover (segment 0 interior tiles,
 // segment 1 ragged tiles and matrices too large for 32-bit offsets), and for
 // the split-bf16 kernels the interior 256 x 256 tiles plus the 128 x 128 tiles
@@ -29,12 +20,25 @@ struct TaskList {
   int rem_cnt[2];
 };
 
+// A work list of the plane products: output tiles of one shape.
+enum PlaneTile { kTileS = 0, kTileM = 1, kTileL = 2 };  // 64 x 64, 128 x 128, 256 x 256
+struct PlaneList {
+  const Task* tasks;
+  int cnt;
+  int tile;  // PlaneTile
+};
+
 // Device tables and buffers inside the caller's workspace, plus the host copies
 // of the few values the launchers need to size grids.
 struct DevTables {
   const MatInfo* mats;
   const Chunk* chunks;  // ISO chunks first, then AVG chunks
   TaskList gram_list, poly_list, update_list;
+  // plane layout (planes = 1): gram and poly, and x at most steps, hold planes
+  // at the offsets of the float buffers (4 bytes per element)
+  int planes;
+  PlaneList gram_pl, poly_pl, update_pl;
+  uint16_t* third;  // third parts of the iterates that bf16x5 updates read as planes: two halves per matrix
   MatScalars* scalars;
   double* part_sq;
   double* part_tr;
@@ -120,8 +124,34 @@ struct PolarStep {
   int arith;        // Arith
   int norm_mode = -1;  // Gram only: -1 none, else the NormMode whose tile partials the Gram
                     // leaves in DevTables::part_norm (kNormFirst: sum A^2, others sum (A - I)^2)
+  // plane layout only: X (and the second operand) is float32, the result is
+  bool x_float = false;
+  bool out_float = false;
+  bool third = false;  // Update: leave the result's third parts too
   NormArgs norm{};  // norm_mode >= 0: the decisions the last tile of each matrix takes
                     // from those partials (norm.mode == norm_mode)
+};
+
+// Arguments of the plane product kernels.
+struct PlaneArgs {
+  const MatInfo* mats;
+  const Task* tasks;
+  MatScalars* sc;
+  const float* xa;      // Gram, Update: X (planes, or float32 if x_float)
+  const float* xa_alt;  // Gram: if set, X of the matrices whose qbuf is 1
+  const float* xb;      // Gram: if set, the second operand (as X)
+  const float* sq;      // Poly: A; Update: P (planes)
+  float* out;           // planes, or float32 if out_float (Update only)
+  int x_float, out_float;
+  const uint16_t* third;  // bf16x5 update on planes: X's third parts
+  uint16_t* third_out;    // Update: if set, the result's
+  float* gpart;
+  int* split_cnt;
+  int* mat_cnt;
+  double* part_norm;
+  const float* coef;
+  int step, n_steps, first, only_active, norm_mode;
+  NormArgs na;
 };
 
 // Initial per-matrix iteration state: steps and result buffer of each class's full schedule
@@ -140,6 +170,8 @@ hipError_t launch_reduce(const DevTables& t, const StepArgs& a, hipStream_t st);
 hipError_t launch_fro(const DevTables& t, const FroArgs& a, hipStream_t st);
 // mode: 0 Gram, 1 polynomial, 2 update
 hipError_t launch_gemm(const DevTables& t, int mode, const PolarStep& p, hipStream_t st);
+// the same products on planes (t.planes)
+hipError_t launch_plane_gemm(const PlaneList& l, int mode, int arith, PlaneArgs g, hipStream_t st);
 // the per-matrix decisions of a phase end without a residual check (only
 // kActStop or kActNone actions: no Gram launch to take them)
 hipError_t launch_gram_norm(const DevTables& t, const NormArgs& a, hipStream_t st);

@@ -11,6 +11,11 @@ constexpr int kBN = 128;
 constexpr int kBK = 16;
 constexpr int kGemmThreads = 256;
 
+// The split-bf16 products run on pre-split operands ("planes", see the product
+// kernels): columns in blocks of kPlaneBlock elements, each its bf16 hi parts
+// followed by its lo parts (4 bytes per element, the offsets of a float buffer).
+constexpr int kPlaneBlock = 32;
+
 // Elements per workgroup of the streaming kernels (reduction, trace, write-back).
 constexpr int kChunk = 4096;
 constexpr int kStreamThreads = 256;
@@ -39,6 +44,7 @@ struct MatInfo {
   int64_t sq_off;    // element offset of this matrix's n x n buffers (Gram, polynomial)
   int64_t part_off;  // element offset of the split-K Gram partials (ksplit * n * n)
   int32_t m, n;      // tall shape
+  int32_t mp, np;    // plane layout: m and n padded to multiples of kPlaneBlock
   int32_t ksplit;    // number of K slices of the Gram product (1 = no split)
   int32_t kchunk;    // rows of X per K slice (multiple of kBK)
   int32_t vec;       // 1 if m and n are multiples of 4 (vector loads allowed)
@@ -46,8 +52,8 @@ struct MatInfo {
   int32_t chunk_begin, chunk_end;  // range of this matrix in the chunk table
   int32_t wide;      // 1 if the tensor is stored wide (rows < cols)
   int32_t sched;     // schedule class (kSchedSquare or kSchedTall)
-  int32_t norm_off;  // first of this matrix's gram_tiles(n) Gram-norm partials
-  int32_t cnt_off;   // split-K Gram: first of its gram_tiles(n) arrival counters (-1 if not split)
+  int32_t norm_off;  // first of this matrix's Gram-norm partials (one per output tile)
+  int32_t cnt_off;   // split-K Gram: first of its output tiles' arrival counters (-1 if not split)
 };
 
 // Output tiles of a symmetric n x n product that are computed: those on or
@@ -60,6 +66,12 @@ __host__ __device__ inline int gram_tiles(int n) {
 __host__ __device__ inline int gram_tile_index(int n, int tm, int tn) {
   const int T = (n + kBM - 1) / kBM;
   return tm * T - tm * (tm - 1) / 2 + (tn - tm);
+}
+
+// The same for square tiles of `tile` outputs.
+__host__ __device__ inline int sym_tiles(int n, int tile) {
+  const int T = (n + tile - 1) / tile;
+  return T * (T + 1) / 2;
 }
 
 // Work item of the streaming kernels: a run of at most kChunk elements of one
