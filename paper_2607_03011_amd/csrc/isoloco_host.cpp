@@ -499,7 +499,12 @@ void plan_plane_lists(isoloco_plan_s* p) {
       // (tiles on the diagonal compute more than they must: 1.25 allows for them)
       if (tiles[kTileL] >= (update ? 256 : 512) && 4 * tiles[kTileL] <= (update ? 1.1 : 1.25) * tiles[kTileM])
         return (int)kTileL;
-      if (tiles[kTileM] >= 160 && 4 * tiles[kTileM] <= 1.6 * tiles[kTileS]) return (int)kTileM;
+      // (a symmetric product whose 128 x 128 tiles just exceed two per CU would
+      // run a second round nearly empty: one round of 256 x 256 tiles, one
+      // matrix of 4096 x 4096 (136 against 528 tiles) 11.09 against 11.57 ms a step)
+      if (!update && tiles[kTileM] > 512 && tiles[kTileM] <= 600 && 4 * tiles[kTileL] <= 1.25 * tiles[kTileM])
+        return (int)kTileL;
+      if (tiles[kTileM] >= (update ? 160 : 120) && 4 * tiles[kTileM] <= 1.6 * tiles[kTileS]) return (int)kTileM;
       return (int)kTileS;
     };
     G.tile = choose(false);

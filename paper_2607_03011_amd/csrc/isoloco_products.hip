@@ -51,10 +51,12 @@ struct TileShape {
 // Waves of 128 x 64, 64 x 64 and 32 x 32.  Two slabs of 32 beat 4 to 5 slabs of
 // 16 in the same LDS on the two large shapes (update of 48 matrices of 768 x 768
 // 135 against 159 us: rows of 64 bytes halve what a line brings); the small one
-// has one tile per CU or less and hides its loads' latency behind three slabs.
+// has few tiles per CU and hides its loads' latency behind two slabs in flight
+// (three slabs of LDS let three workgroups share a CU: one d = 768 block, 312 to
+// 624 tiles a launch, 1309 -> 1237 us a step against four slabs).
 typedef TileShape<256, 256, 2, 4, 2> TileL;
 typedef TileShape<128, 128, 2, 2, 2> TileM;
-typedef TileShape<64, 64, 2, 2, 4> TileS;
+typedef TileShape<64, 64, 2, 2, 3> TileS;
 constexpr int kSlabK = 32;
 
 // 16 bytes per lane from memory to LDS: lane l's bytes land at lds_off + 16 l
