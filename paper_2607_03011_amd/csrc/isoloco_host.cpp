@@ -1032,8 +1032,6 @@ static isoloco_plan_s* build_plan(const isoloco_tensor* layout, int32_t n_tensor
     double l = p->phase_bound[kSchedTall][0];
     for (int k = 1; k <= e1 - 3; ++k) {
       l = peval(&sc[3 * (k - 1)], l);
-      // (on planes A M takes no third part of A: not before the bf16x5 steps end)
-      if (p->planes && o.precision == ISOLOCO_PREC_MIXED && k + 1 < kX6Steps) continue;
       if (l >= kFactorMinBound && (e1 - k) % 2 == 1) {
         p->cont_from = k;
         p->cont_to = e1;
@@ -1149,6 +1147,15 @@ isoloco_status isoloco_plan(const isoloco_tensor* layout, int32_t n_tensors, int
         if (std::max(layout[i].rows, layout[i].cols) > kPlaneMaxRows) planes = false;
       }
     p = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
+    // On planes A M of the factored steps has no third part of A: a window that
+    // starts while the updates still take one (a first bound near 1) keeps
+    // float32 operands.
+    if (planes && o.precision == ISOLOCO_PREC_MIXED && p->cont_to > 0 && p->cont_from + 1 < kX6Steps) {
+      planes = false;
+      isoloco_plan_s* q = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
+      std::swap(p, q);
+      delete q;
+    }
     // The padding of many small matrices can take a plan past the static
     // workspace that would fit without it: such a plan keeps float32 operands.
     if (planes && p->total > ISOLOCO_STATIC_WORKSPACE_BYTES && 12 * iso <= (int64_t)ISOLOCO_STATIC_WORKSPACE_BYTES) {
