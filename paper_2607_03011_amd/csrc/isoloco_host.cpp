@@ -1395,15 +1395,7 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
           pp.step = k;
           pp.only_active = 1;
           pp.arith = step_arith(prec, k, kProdPoly);
-          // (plane layout) A and M commute: B is symmetric too
-          PolarStep ps2 = pb;
-          ps2.xin = tt.gram;
-          ps2.bin = cur;
-          DevTables t2 = tc;
-          t2.gram = tt.poly;
-          if ((q = timed_on(s, plan->planes ? kPhGram : kPhUpdate, [&] {
-                return plan->planes ? launch_gemm(t2, 0, ps2, s) : launch_gemm(ta, 2, pa, s);
-              })) != hipSuccess ||
+          if ((q = timed_on(s, kPhUpdate, [&] { return launch_gemm(ta, 2, pa, s); })) != hipSuccess ||
               (q = timed_on(s, kPhGram, [&] { return launch_gemm(tb, 0, pb, s); })) != hipSuccess ||
               (q = timed_on(s, kPhPoly, [&] { return launch_gemm(tp, 1, pp, s); })) != hipSuccess ||
               (q = timed_on(s, kPhGram, [&] { return launch_gemm(tb, 0, pb, s); })) != hipSuccess)
