@@ -291,6 +291,24 @@ isoloco_status isoloco_schedule_phases(isoloco_plan_t plan, int32_t tall, int32_
  * (isoloco_options.factored); both 0 when none.  Host only. */
 isoloco_status isoloco_factored_steps(isoloco_plan_t plan, int32_t* first, int32_t* end);
 
+/* How a plan's matrix products run (tests and the benchmark's accounting).  In
+ * the mixed and bf16x3 modes the iterates and the n x n matrices are kept as
+ * the bfloat16 parts the products read ("planes") unless a matrix has more
+ * than 2^21 - 32 rows, the planes' padding to multiples of 32 would cost the
+ * plan its place in the static workspace, or the factored steps would start at
+ * step 1; the parts per product are the mode's either way.  Host only. */
+typedef struct {
+  int32_t planes;             /* 1: planes; 0: float32 operands                       */
+  int32_t third;              /* 1: planes with the third parts of the first iterates */
+  int32_t update_parts_early; /* part products of the updates of the first 3 steps    */
+  int32_t parts;              /* part products of every other product (1: float32)    */
+  /* planes, per class (0 square-ish, 1 tall): the side of the output tiles of
+   * its launches (0: no matrix of the class)                                       */
+  int32_t gram_tile[2], poly_tile[2], update_tile[2];
+} isoloco_products;
+
+isoloco_status isoloco_get_products(isoloco_plan_t plan, isoloco_products* out);
+
 /* Per-kernel timing of the last aggregate, measured with HIP events recorded
  * on the aggregate's stream around every launch (enable first; the events
  * add a few microseconds per launch).  Not part of the operation itself. */

@@ -16,7 +16,7 @@ __all__ = [
     "isoloco_get_stats", "isoloco_schedule", "isoloco_schedule_phases", "isoloco_plan_destroy",
     "isoloco_status_string", "isoloco_last_error", "isoloco_enable_timing", "isoloco_get_timing",
     "isoloco_timing", "isoloco_aggregate_static", "ISOLOCO_STATIC_WORKSPACE_BYTES",
-    "isoloco_factored_steps",
+    "isoloco_factored_steps", "isoloco_get_products", "isoloco_products",
     "IsoLoCoPlan", "LIB_PATH", "EXPORTED_SYMBOLS",
 ]
 
@@ -52,7 +52,7 @@ EXPORTED_SYMBOLS = (
     "isoloco_plan", "isoloco_workspace_size", "isoloco_set_workspace", "isoloco_aggregate",
     "isoloco_get_stats", "isoloco_schedule", "isoloco_schedule_phases", "isoloco_plan_destroy",
     "isoloco_status_string", "isoloco_last_error", "isoloco_enable_timing", "isoloco_get_timing",
-    "isoloco_aggregate_static", "isoloco_factored_steps",
+    "isoloco_aggregate_static", "isoloco_factored_steps", "isoloco_get_products",
 )
 
 
@@ -74,6 +74,12 @@ class isoloco_tensor_stats(ctypes.Structure):
     _fields_ = [("sigma_bar", ctypes.c_float), ("fro_norm", ctypes.c_float),
                 ("orth_resid", ctypes.c_float), ("steps", ctypes.c_int32),
                 ("flags", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+class isoloco_products(ctypes.Structure):
+    _fields_ = [("planes", ctypes.c_int32), ("third", ctypes.c_int32), ("update_parts_early", ctypes.c_int32),
+                ("parts", ctypes.c_int32), ("gram_tile", ctypes.c_int32 * 2), ("poly_tile", ctypes.c_int32 * 2),
+                ("update_tile", ctypes.c_int32 * 2)]
 
 
 class isoloco_timing(ctypes.Structure):
@@ -112,6 +118,7 @@ _sig = {
     "isoloco_schedule_phases": (ctypes.c_int, [_P, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32), ctypes.c_int32,
                                                ctypes.POINTER(ctypes.c_int32)]),
     "isoloco_factored_steps": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]),
+    "isoloco_get_products": (ctypes.c_int, [_P, ctypes.POINTER(isoloco_products)]),
     "isoloco_plan_destroy": (ctypes.c_int, [_P]),
     "isoloco_enable_timing": (ctypes.c_int, [_P, ctypes.c_int32]),
     "isoloco_get_timing": (ctypes.c_int, [_P, ctypes.POINTER(isoloco_timing)]),
@@ -221,6 +228,13 @@ def isoloco_factored_steps(plan):
     return a.value, b.value
 
 
+def isoloco_get_products(plan):
+    """How the plan's matrix products run (an isoloco_products)."""
+    p = isoloco_products()
+    _check(_lib.isoloco_get_products(plan, ctypes.byref(p)), "isoloco_get_products")
+    return p
+
+
 def isoloco_enable_timing(plan, enable=True):
     _check(_lib.isoloco_enable_timing(plan, 1 if enable else 0), "isoloco_enable_timing")
 
@@ -314,6 +328,9 @@ class IsoLoCoPlan:
 
     def factored_steps(self):
         return isoloco_factored_steps(self.handle)
+
+    def products(self):
+        return isoloco_get_products(self.handle)
 
     def close(self):
         if self.handle is not None:

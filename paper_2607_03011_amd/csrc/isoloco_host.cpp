@@ -125,7 +125,10 @@ int step_arith(int precision, int k, int product) {
   }
 }
 // Matrices with more rows than this keep the products on float32 operands (the
-// plane kernels address a tile's rows with 32-bit offsets).
+// plane kernels address a tile's rows with 32-bit offsets).  Such a plan runs
+// the part products its mode asks for, on the kernels that split float32: one
+// matrix of (2^21 + 64) x 64 144 ms a step, x 768 1027 ms (198 and 1162 ms in
+// bf16x6).
 constexpr int64_t kPlaneMaxRows = ((int64_t)1 << 21) - kPlaneBlock;
 // The array of third parts takes 4 bytes per element of the corrected matrices
 // (less what the factored steps then share): up to this size.
@@ -979,12 +982,6 @@ hipError_t upload_tables(const isoloco_plan_s* plan, char* w) {
   return hipStreamSynchronize(nullptr);
 }
 
-// Arithmetic of a plan's products: without planes the split modes run bf16x6
-// (every product at least as accurate as the mode asks for).
-int polar_precision(const isoloco_plan_s* p) {
-  return p->planes || p->opts.precision == ISOLOCO_PREC_FP32 ? p->opts.precision : ISOLOCO_PREC_BF16X6;
-}
-
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
   return x < y + nb && y < x + na;
@@ -1148,8 +1145,9 @@ isoloco_status isoloco_plan(const isoloco_tensor* layout, int32_t n_tensors, int
       }
     p = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
     // On planes A M of the factored steps has no third part of A: a window that
-    // starts while the updates still take one (a first bound near 1) keeps
-    // float32 operands.
+    // starts while the updates still take one keeps float32 operands (a tall
+    // first bound of 0.05 to 0.17, where the window is (1, 4); the 12-block
+    // d = 768 model with 0.1: 8.25 ms a step, 12.42 in bf16x6).
     if (planes && o.precision == ISOLOCO_PREC_MIXED && p->cont_to > 0 && p->cont_from + 1 < kX6Steps) {
       planes = false;
       isoloco_plan_s* q = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
@@ -1299,7 +1297,7 @@ static isoloco_status aggregate_on(isoloco_plan_t plan, char* ws, bool use_side,
     const bool two = use_side && plan->opts.streams == 2 && plan->side && n_cls[0] > 0 && n_cls[1] > 0;
     plan->last_streams = two ? 2 : 1;
     const char* what = "";
-    const int prec = polar_precision(plan);
+    const int prec = plan->opts.precision;
     // The polar iteration of the matrices of class cls (-1: every matrix) on
     // stream s, from the scalars fro_kernel set (tt.scalars; the matrices are
     // in tt.delta); the factor of matrix m ends in tt.x[scalars[m].qbuf].
@@ -1770,6 +1768,31 @@ isoloco_status isoloco_factored_steps(isoloco_plan_t plan, int32_t* first, int32
   if (!plan || !first || !end) return fail(ISOLOCO_ERR_INVALID_ARG, "NULL argument");
   *first = plan->cont_from;
   *end = plan->cont_to;
+  return ISOLOCO_OK;
+}
+
+isoloco_status isoloco_get_products(isoloco_plan_t plan, isoloco_products* out) {
+  if (!plan || !out) return fail(ISOLOCO_ERR_INVALID_ARG, "NULL argument");
+  auto parts = [&](int k) {
+    switch (step_arith(plan->opts.precision, k, kProdUpdate)) {
+      case kArithFp32: return 1;
+      case kArithBf16x6: return 6;
+      case kArithBf16x5: return 5;
+      default: return 3;
+    }
+  };
+  *out = isoloco_products{};
+  out->planes = plan->planes ? 1 : 0;
+  out->third = plan->third ? 1 : 0;
+  out->update_parts_early = parts(0);
+  out->parts = parts(kX6Steps);
+  if (!plan->planes) return ISOLOCO_OK;
+  auto tiles = [](const PlaneListHost& l) { return l.tasks.empty() ? 0 : kTileSide[l.tile]; };
+  for (int c = 0; c < kSchedClasses; ++c) {
+    out->gram_tile[c] = tiles(plan->gram_plc[c]);
+    out->poly_tile[c] = tiles(plan->poly_plc[c]);
+    out->update_tile[c] = tiles(plan->update_plc[c]);
+  }
   return ISOLOCO_OK;
 }
 

@@ -6,8 +6,9 @@
 //                 layout), and the whole Nesterov step (Algorithm 2) for
 //                 tensors that are not corrected.
 //   fro           per-matrix Frobenius norm from the partials (pre-scaling).
-//   gemm          batched, grouped MFMA products (bf16x6 or fp32; the other split
-//                 modes: isoloco_products.hip) for the polar iteration:
+//   gemm          batched, grouped MFMA products on float32 operands for the polar
+//                 iteration (split-bf16 or fp32; most plans in the mixed and bf16x3
+//                 modes run those of isoloco_products.hip instead):
 //                 Gram A = X^T X, polynomial P' = g (a I + b g^2 A + c g^4 A^2),
 //                 update X <- X P'.
 //   gram_norm     ||A||_F (first step: normalisation) or ||A - I||_F (check).
@@ -855,7 +856,7 @@ __device__ __forceinline__ void gram_epilogue(const GemmArgs& g, const GemmSetup
     sq = block_sum256(sq, red);
     if (threadIdx.x == 0) {
       partial_store(g.part_norm + mi.norm_off + tile, diag ? sq : 2.0 * sq);
-      if (arrive(g.mat_cnt + task.mat, gram_tiles(n))) 
+      if (arrive(g.mat_cnt + task.mat, gram_tiles(n)))
         norm_decide(mi, g.part_norm, g.sc_out[task.mat], g.na, gram_tiles(n));
     }
   }
@@ -976,14 +977,17 @@ __global__ void __launch_bounds__(kGemmThreads, 2) gemm_f32_kernel(GemmArgs g) {
 }
 
 // ---------------------------------------------------------------------------
-// Split-bfloat16 main loop (bf16x6)
+// Split-bfloat16 main loop (bf16x3, bf16x5 and bf16x6)
 // ---------------------------------------------------------------------------
 //
-// Each fp32 operand x is split into NS = 3 bfloat16 parts, x = x0 + x1 + x2 + r,
+// Each fp32 operand x is split into NS bfloat16 parts, x = x0 + x1 (+ x2) + r,
 // x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1), round to nearest
-// even, so |r| <= 2^-24 |x|.  The product sum_k a_k b_k is accumulated in fp32
-// over the part products of order i + j <= 2:
-//   a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1 + a0 b0
+// even, so |r| <= 2^-16 |x| for NS = 2 and 2^-24 |x| for NS = 3.  The product
+// sum_k a_k b_k is accumulated in fp32 over the part products of order
+// i + j <= 2 that both splits provide:
+//   bf16x3 (2 + 2 parts):  a1 b0 + a0 b1 + a0 b0
+//   bf16x5 (3 + 2 parts):  a2 b0 + a1 b1 + a1 b0 + a0 b1 + a0 b0
+//   bf16x6 (3 + 3 parts):  a2 b0 + a1 b1 + a0 b2 + a1 b0 + a0 b1 + a0 b0
 // on v_mfma_f32_32x32x16_bf16.  K is staged in slabs of 32: fp32 global loads
 // into registers (next slab in flight during the current slab's products),
 // split, and stored to LDS as NS bf16 planes per operand in [row][k] order, so
@@ -1190,15 +1194,21 @@ __device__ __forceinline__ void store_operand(const Slab32& r, __bf16 (*planes)[
   else slab32_store<NS, SCALED, ROWS, LK>(r, planes, scale);
 }
 
-// Split-bf16 arithmetic with NP part products per fp32 product, both operands
-// in 3 parts (bf16x6; the 3 and 5 part products of the other split modes run
-// on the plane kernels).
+// Split-bf16 arithmetic with NP part products per fp32 product: NP = 3
+// (bf16x3: both operands in 2 parts, products of part orders 0 + 0, 0 + 1,
+// 1 + 0), NP = 6 (bf16x6: 3 parts each, all orders up to 2) and NP = 5 (left
+// operand in 3 parts, right operand in 2: the orders up to 2 without the
+// right operand's third part).  NP = 5 serves the update X' = X P': a
+// rounding error of X enters every direction of X' with the size of X's
+// largest singular values, while an error of P' enters the component of
+// each singular direction in proportion to its singular value, so the left
+// factor needs the third part and the right factor does not.
 template <int NP>
 struct SplitParts {
-  static_assert(NP == 6, "bf16x6");
-  static constexpr int a = 3;   // planes of the left operand
-  static constexpr int b = 3;   // planes of the right operand
-  static constexpr int nb = 1;  // LDS buffers
+  static_assert(NP == 3 || NP == 5 || NP == 6, "bf16x3, bf16x5 or bf16x6");
+  static constexpr int a = NP == 3 ? 2 : 3;   // planes of the left operand
+  static constexpr int b = NP == 6 ? 3 : 2;   // planes of the right operand
+  static constexpr int nb = NP == 3 ? 2 : 1;  // LDS buffers (double-buffered bf16x3)
 };
 
 // One k16 substep of a wave's (32 NA) x 64 tile: read the operand fragments
@@ -1280,14 +1290,20 @@ __device__ __forceinline__ void store_update_colmajor(const GemmArgs& g, const G
   }
 }
 
-// One LDS buffer, two barriers per slab: three parts of both operands leave no
-// room for a second.
+// bf16x3 (NP = 3) double-buffers the LDS slabs: while the products of slab s
+// run from one buffer, slab s + 1 is split and stored into the other and the
+// global loads of slab s + 2 are in flight; one barrier per slab, and the
+// steady-state loop body is a single basic block (the look-ahead slab index
+// is clamped to the last slab instead of branching), so that the compiler can
+// interleave the split arithmetic with the matrix products.  bf16x5 and
+// bf16x6 need 1.25x and 1.5x the LDS per buffer and keep a single buffer
+// with two barriers.
 // SCALED: the X operands are multiplied by the first step's 1/||Delta||_F.
 template <int MODE, int NP, int LAYOUT, bool SCALED, bool SAME = false>
 __device__ __forceinline__ void bf16_tile(const GemmArgs& g, const Task& task,
                                           __bf16 (*Ap)[SplitParts<NP>::a][kBM][kLdsK],
                                           __bf16 (*Bp)[SplitParts<NP>::b][kBN][kLdsK]) {
-  constexpr int kNa = SplitParts<NP>::a, kNb = SplitParts<NP>::b;
+  constexpr int kNa = SplitParts<NP>::a, kNb = SplitParts<NP>::b, NB = SplitParts<NP>::nb;
   // only X operands carry a scale (Gram: both, Update: A)
   constexpr bool SA = SCALED && MODE != kPoly;
   constexpr bool SB = SCALED && MODE == kGram;
@@ -1307,6 +1323,52 @@ __device__ __forceinline__ void bf16_tile(const GemmArgs& g, const Task& task,
   if (nslab > 0) {
   load_operand<MODE, LAYOUT>(s.A, s.k_begin, s.i0, ra);
   if constexpr (!SAME) load_operand<MODE, LAYOUT>(s.B, s.k_begin, s.j0, rb);
+  if (NB == 2) {
+    // Registers hold two slabs in flight: at the top of the products of slab
+    // sl, slab sl + 1 is in (ra1, rb1) and slab sl + 2 in (ra, rb).  Each
+    // iteration splits and stores the first into the idle LDS buffer and
+    // reloads its registers with slab sl + 3, so a load has about two slabs of
+    // products to land.  The loop is unrolled by two so that the register
+    // roles are static.
+    auto kat = [&](int sl) { return min(s.k_begin + sl * kBK2, klast); };
+    Slab32 ra1, rb1;
+    load_operand<MODE, LAYOUT>(s.A, kat(1), s.i0, ra1);
+    if constexpr (!SAME) load_operand<MODE, LAYOUT>(s.B, kat(1), s.j0, rb1);
+    store_operand<MODE, LAYOUT, kNa, SA>(ra, Ap[0], s.A.scale);
+    if constexpr (!SAME) store_operand<MODE, LAYOUT, kNb, SB>(rb, Bp[0], s.B.scale);
+    load_operand<MODE, LAYOUT>(s.A, kat(2), s.i0, ra);
+    if constexpr (!SAME) load_operand<MODE, LAYOUT>(s.B, kat(2), s.j0, rb);
+    __syncthreads();
+    int sl = 0;
+    for (; sl + 2 < nslab; sl += 2) {
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 0, acc);
+      store_operand<MODE, LAYOUT, kNa, SA>(ra1, Ap[1], s.A.scale);
+      if constexpr (!SAME) store_operand<MODE, LAYOUT, kNb, SB>(rb1, Bp[1], s.B.scale);
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 16, acc);
+      load_operand<MODE, LAYOUT>(s.A, kat(sl + 3), s.i0, ra1);
+      if constexpr (!SAME) load_operand<MODE, LAYOUT>(s.B, kat(sl + 3), s.j0, rb1);
+      __syncthreads();
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[1], bpl(1), 0, acc);
+      store_operand<MODE, LAYOUT, kNa, SA>(ra, Ap[0], s.A.scale);
+      if constexpr (!SAME) store_operand<MODE, LAYOUT, kNb, SB>(rb, Bp[0], s.B.scale);
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[1], bpl(1), 16, acc);
+      load_operand<MODE, LAYOUT>(s.A, kat(sl + 4), s.i0, ra);
+      if constexpr (!SAME) load_operand<MODE, LAYOUT>(s.B, kat(sl + 4), s.j0, rb);
+      __syncthreads();
+    }
+    // one or two slabs remain: slab sl in buffer 0, slab sl + 1 in (ra1, rb1)
+    int last = 0;
+    if (sl + 1 < nslab) {
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 0, acc);
+      store_operand<MODE, LAYOUT, kNa, SA>(ra1, Ap[1], s.A.scale);
+      if constexpr (!SAME) store_operand<MODE, LAYOUT, kNb, SB>(rb1, Bp[1], s.B.scale);
+      mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 16, acc);
+      __syncthreads();
+      last = 1;
+    }
+    mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[last], bpl(last), 0, acc);
+    mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[last], bpl(last), 16, acc);
+  } else {
     for (int sl = 0; sl < nslab; ++sl) {
       __syncthreads();
       store_operand<MODE, LAYOUT, kNa, SA>(ra, Ap[0], s.A.scale);
@@ -1318,6 +1380,7 @@ __device__ __forceinline__ void bf16_tile(const GemmArgs& g, const Task& task,
       mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 0, acc);
       mfma_substep<kNa, kNb, 2, 2, kBM>(Ap[0], bpl(0), 16, acc);
     }
+  }
   }
   if constexpr (MODE == kUpdate && LAYOUT == kFast)
     store_update_colmajor<2, 2>(g, s, acc, reinterpret_cast<float*>(&Ap[0][0][0][0]));
@@ -1362,15 +1425,23 @@ __global__ void __launch_bounds__(kGemmThreads, 2) gemm_bf16_kernel(GemmArgs g) 
 // column-major iterates; the planner lists 256 x 256 tiles for the updates
 // alone), so that every fp32 operand value staged through LDS feeds twice as
 // many products as on 128 x 128 tiles -- half the global loads, splits, LDS
-// writes and barriers per product.  One buffer of 3 + 3 planes (120 KB) and two
-// barriers per slab, 512 threads in 8 waves of 128 x 64 (2 x 4).
+// writes and barriers per product.  bf16x3 and bf16x5 double-buffer LDS (the
+// whole 160 KB of the CU: 2 buffers of 2 + 2 planes of 80-byte rows, or of
+// 3 + 2 planes of 64-byte rows) on 1024 threads (gemm_bf16_big16_kernel);
+// bf16x6 keeps one buffer of 3 + 3 planes (120 KB) and two barriers per slab,
+// on 512 threads in 8 waves of 128 x 64 (2 x 4) (gemm_bf16_big_kernel).
 constexpr int kBig = 256;
 constexpr int kBigThreads = 512;
 
+// LDS of the 256 x 256 kernel: bf16x3 double-buffers 80-byte rows (2 x 2 x 2
+// planes of 256 rows: 160 KB); bf16x5 double-buffers 64-byte rows (2 x (3 + 2)
+// planes: 160 KB; with 80-byte rows one buffer only, two barriers per slab:
+// its updates took 2.6x the time of a bf16x3 update for 1.67x the products);
+// bf16x6 keeps one buffer of 80-byte rows.
 template <int NP>
 struct BigLds {
-  static constexpr int nb = 1;        // LDS buffers
-  static constexpr int lk = kLdsK;    // row pitch (bf16 elements)
+  static constexpr int nb = NP == 6 ? 1 : 2;            // LDS buffers
+  static constexpr int lk = NP == 5 ? kBK2 : kLdsK;     // row pitch (bf16 elements)
 };
 
 template <int MODE, int NP, bool SCALED>
@@ -1378,6 +1449,7 @@ __device__ __forceinline__ void bf16_big_tile(const GemmArgs& g, const Task& tas
                                               __bf16 (*Ap)[SplitParts<NP>::a][kBig][BigLds<NP>::lk],
                                               __bf16 (*Bp)[SplitParts<NP>::b][kBig][BigLds<NP>::lk]) {
   static_assert(MODE == kUpdate, "256 x 256 tiles serve the update products");
+  static_assert(BigLds<NP>::nb == 1, "the double-buffered updates run on gemm_bf16_big16_kernel");
   constexpr int LAYOUT = kFast;
   constexpr int kNa = SplitParts<NP>::a, kNb = SplitParts<NP>::b, LK = BigLds<NP>::lk;
   constexpr bool SA = SCALED;  // the X operand carries the first step's scale
@@ -1421,6 +1493,102 @@ __global__ void __launch_bounds__(kBigThreads, 1) gemm_bf16_big_kernel(GemmArgs 
   __shared__ __attribute__((aligned(16))) char lds[kPlanes > kStage ? kPlanes : kStage];
   bf16_big_tile<MODE, NP, SCALED>(g, task, reinterpret_cast<APlanes*>(lds),
                                   reinterpret_cast<BPlanes*>(lds + NB * sizeof(APlanes)));
+}
+
+// The bf16x3 and bf16x5 updates' 256 x 256 tiles run on 1024 threads: 16 waves
+// of 64 x 64 (4 x 4), four per SIMD instead of two, each thread staging 8
+// values of each operand per slab (one slab in flight in registers), the same
+// double-buffered LDS as the 512-thread kernel and the same products in the
+// same order per output element (bit for bit the same results).  The two
+// extra waves per SIMD hide more of the operand latency: update launches 3%
+// (109.5M workload) to 5% (341M) shorter.  bf16x6 keeps the 512-thread kernel
+// (one LDS buffer).
+constexpr int kBig16Threads = 1024;
+
+// 8 values of an i-contiguous operand: row i0 + t % ROWS, k = k0 + 8 (t / ROWS) .. +7
+template <int ROWS>
+__device__ __forceinline__ void slab16_load_icontig(const Operand& op, int k0, int i0, floatx4 (&r)[2]) {
+  const int t = threadIdx.x;
+  const int bytes = 4 * ((op.K - 1) * (int)op.s_k + (op.I - 1) * (int)op.s_i + 1);
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(op.base), (short)0, bytes, kBufferFlags);
+  const int kb = k0 + 8 * __builtin_amdgcn_readfirstlane(t / ROWS);
+  const int vo = 4 * (i0 + t % ROWS);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      r[q][e] = __builtin_bit_cast(
+          float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, 4 * (kb + 4 * q + e) * (int)op.s_k, 0));
+}
+
+// Split the thread's 8 values into NS bf16 parts (as slab32_store) and store
+// each part plane as one 16-byte row segment.
+template <int NS, bool SCALED, int ROWS, int LK>
+__device__ __forceinline__ void slab16_store(const floatx4 (&r)[2], __bf16 (*planes)[ROWS][LK], float scale) {
+  const int t = threadIdx.x;
+  const int i = t % ROWS, c = t / ROWS;
+  bf16x8 part[NS];
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {
+    floatx2 x = {r[e / 4][e % 4], r[e / 4][e % 4 + 1]};
+    if (SCALED) x *= scale;
+#pragma unroll
+    for (int p = 0; p < NS; ++p) {
+      const bf16x2 h = __builtin_convertvector(x, bf16x2);
+      part[p][e] = h[0];
+      part[p][e + 1] = h[1];
+      if (p + 1 < NS) x -= __builtin_convertvector(h, floatx2);
+    }
+  }
+#pragma unroll
+  for (int p = 0; p < NS; ++p) *reinterpret_cast<bf16x8*>(&planes[p][i][lds_chunk<LK>(i, c)]) = part[p];
+}
+
+template <int NP, bool SCALED>
+__global__ void __launch_bounds__(kBig16Threads, 1) gemm_bf16_big16_kernel(GemmArgs g) {
+  constexpr int MODE = kUpdate;
+  static_assert(BigLds<NP>::nb == 2, "double-buffered LDS");
+  constexpr int kNa = SplitParts<NP>::a, kNb = SplitParts<NP>::b, LK = BigLds<NP>::lk;
+  typedef __bf16 APlanes[kNa][kBig][LK];
+  typedef __bf16 BPlanes[kNb][kBig][LK];
+  constexpr size_t kPlanes = 2 * (sizeof(APlanes) + sizeof(BPlanes));
+  constexpr size_t kStage = stage_floats<2>(kBig16Threads / 64) * sizeof(float);
+  __shared__ __attribute__((aligned(16))) char lds[kPlanes > kStage ? kPlanes : kStage];
+  const Task task = g.tasks[blockIdx.x];
+  if (task.mat < 0 || (g.only_active && !g.sc[task.mat].active)) return;
+  APlanes* Ap = reinterpret_cast<APlanes*>(lds);
+  BPlanes* Bp = reinterpret_cast<BPlanes*>(lds + 2 * sizeof(APlanes));
+  const GemmSetup s = gemm_setup<MODE, kBig>(g, task);
+  floatx16 acc[2][2];
+  gemm_acc_init<MODE, 2, 4>(g, s, acc);
+  const int nslab = (s.k_end - s.k_begin + kBK2 - 1) / kBK2;
+  if (nslab > 0) {
+    const int klast = s.k_begin + (nslab - 1) * kBK2;
+    auto kat = [&](int sl) { return min(s.k_begin + sl * kBK2, klast); };
+    floatx4 ra[2], rb[2];
+    slab16_load_icontig<kBig>(s.A, s.k_begin, s.i0, ra);
+    slab16_load_icontig<kBig>(s.B, s.k_begin, s.j0, rb);
+    slab16_store<kNa, SCALED, kBig, LK>(ra, Ap[0], s.A.scale);
+    slab16_store<kNb, false, kBig, LK>(rb, Bp[0], s.B.scale);
+    slab16_load_icontig<kBig>(s.A, kat(1), s.i0, ra);
+    slab16_load_icontig<kBig>(s.B, kat(1), s.j0, rb);
+    __syncthreads();
+    for (int sl = 0; sl + 1 < nslab; ++sl) {
+      const int cur = sl & 1;
+      mfma_substep<kNa, kNb, 2, 4, kBig, LK>(Ap[cur], Bp[cur], 0, acc);
+      slab16_store<kNa, SCALED, kBig, LK>(ra, Ap[cur ^ 1], s.A.scale);
+      slab16_store<kNb, false, kBig, LK>(rb, Bp[cur ^ 1], s.B.scale);
+      mfma_substep<kNa, kNb, 2, 4, kBig, LK>(Ap[cur], Bp[cur], 16, acc);
+      slab16_load_icontig<kBig>(s.A, kat(sl + 2), s.i0, ra);
+      slab16_load_icontig<kBig>(s.B, kat(sl + 2), s.j0, rb);
+      __syncthreads();
+    }
+    const int last = (nslab - 1) & 1;
+    mfma_substep<kNa, kNb, 2, 4, kBig, LK>(Ap[last], Bp[last], 0, acc);
+    mfma_substep<kNa, kNb, 2, 4, kBig, LK>(Ap[last], Bp[last], 16, acc);
+  }
+  store_update_colmajor<2, 4>(g, s, acc, reinterpret_cast<float*>(lds));
 }
 
 // The per-matrix decisions of a phase end without a Gram launch (kActStop
@@ -1684,7 +1852,10 @@ static void launch_big_cover(const TaskList& L, const GemmArgs& g0, hipStream_t 
   if constexpr (MODE == kUpdate) {
     if (L.big_cnt) {
       g.tasks = L.tasks + L.big_off;
-      hipLaunchKernelGGL((gemm_bf16_big_kernel<MODE, NP, SCALED>), dim3(L.big_cnt), block, 0, st, g);
+      if constexpr (NP == 3 || NP == 5)
+        hipLaunchKernelGGL((gemm_bf16_big16_kernel<NP, SCALED>), dim3(L.big_cnt), dim3(kBig16Threads), 0, st, g);
+      else
+        hipLaunchKernelGGL((gemm_bf16_big_kernel<MODE, NP, SCALED>), dim3(L.big_cnt), block, 0, st, g);
     }
   }
   launch_bf16_segments<MODE, NP, SCALED>(L.tasks, L.rem_off, L.rem_cnt, g0, st);
@@ -1705,8 +1876,12 @@ static void launch_mode(const TaskList& L, const GemmArgs& g0, int arith, hipStr
     g.tasks = L.tasks;
     const int n = L.seg_cnt[0] + L.seg_cnt[1];
     if (n) hipLaunchKernelGGL(gemm_f32_kernel<MODE>, dim3(n), dim3(kGemmThreads), 0, st, g);
-  } else {
+  } else if (arith == kArithBf16x6) {
     launch_bf16<MODE, 6>(L, g0, st);
+  } else if (MODE == kUpdate && arith == kArithBf16x5) {
+    launch_bf16<MODE, 5>(L, g0, st);
+  } else {
+    launch_bf16<MODE, 3>(L, g0, st);
   }
 }
 

@@ -291,3 +291,23 @@ def test_factored_steps_window():
         h = iso.isoloco_plan(layout, 20544, 4, 0, opts)
         assert iso.isoloco_factored_steps(h) == (0, 0), opts
         iso.isoloco_plan_destroy(h)
+
+
+# a tall first bound whose factored steps would start at step 1 (in the mixed
+# mode), a matrix of more than 2^21 - 32 rows: plans that keep float32 operands
+FLOAT32_OPERANDS = [([(0, 768, 256, 0), (196608, 64, 64, 0)], dict(phase_tall=(0.1, -1.0, -1.0))),
+                    ([(0, 2097121, 64, 0)], {})]
+
+
+@pytest.mark.parametrize("precision, parts", [(0, (5, 3)), (1, (1, 1)), (2, (3, 3)), (3, (6, 6))],
+                         ids=["mixed", "fp32", "bf16x3", "bf16x6"])
+def test_part_products_are_the_modes(precision, parts):
+    """The part products per product are those of the precision mode, on pre-split
+    and on float32 operands alike."""
+    for layout, opts in FLOAT32_OPERANDS + [(LAY, {}), ([(0, 2097120, 64, 0)], {})]:
+        h = iso.isoloco_plan(layout, max(o + r * c for o, r, c, _ in layout), 2, 0, dict(opts, precision=precision))
+        p = iso.isoloco_get_products(h)
+        iso.isoloco_plan_destroy(h)
+        assert (p.update_parts_early, p.parts) == parts
+        keeps = (layout, opts) in FLOAT32_OPERANDS[precision // 2:]
+        assert p.planes == (precision in (0, 2) and not keeps)

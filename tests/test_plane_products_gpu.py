@@ -104,3 +104,19 @@ def test_small_matrices_static_step(iso):
     lay, n, w, _, mom, st = _step(iso, shapes, 4, seed=3, static=True)
     # (a 2 x 2 Gaussian matrix may be nearly singular: the 5 x 4 ones)
     _check(lay, n, w, mom, st, select=[1, 3, 11999])
+
+
+@pytest.mark.gpu
+def test_float32_operands_run_the_modes_products(iso):
+    """A plan that keeps float32 operands (its factored steps would start at step
+    1) runs the products of its mode: mixed, bf16x3 and bf16x6 all match the
+    oracle, with different rounding."""
+    moms = []
+    for precision in (iso.ISOLOCO_PREC_MIXED, iso.ISOLOCO_PREC_BF16X3, iso.ISOLOCO_PREC_BF16X6):
+        lay, n, w, _, mom, st = _step(iso, [(768, 256), (200, 600), (320, 256), (70, 50)], 4,
+                                      dict(precision=precision, phase_tall=(0.1, -1.0, -1.0)), seed=4)
+        _check(lay, n, w, mom, st)
+        moms.append(mom)
+    for i in range(3):
+        for j in range(i):
+            assert not np.array_equal(moms[i], moms[j]), (i, j)
