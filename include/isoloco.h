@@ -295,8 +295,9 @@ isoloco_status isoloco_factored_steps(isoloco_plan_t plan, int32_t* first, int32
  * the mixed and bf16x3 modes the iterates and the n x n matrices are kept as
  * the bfloat16 parts the products read ("planes") unless a matrix has more
  * than 2^21 - 32 rows, the planes' padding to multiples of 32 would cost the
- * plan its place in the static workspace, or the factored steps would start at
- * step 1; the parts per product are the mode's either way.  Host only. */
+ * plan its place in the static workspace or more than double a larger one, or
+ * (mixed) the factored steps would start at step 1; the parts per product are
+ * the mode's either way.  Host only. */
 typedef struct {
   int32_t planes;             /* 1: planes; 0: float32 operands                       */
   int32_t third;              /* 1: planes with the third parts of the first iterates */

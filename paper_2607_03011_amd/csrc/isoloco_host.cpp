@@ -130,6 +130,11 @@ int step_arith(int precision, int k, int product) {
 // matrix of (2^21 + 64) x 64 144 ms a step, x 768 1027 ms (198 and 1162 ms in
 // bf16x6).
 constexpr int64_t kPlaneMaxRows = ((int64_t)1 << 21) - kPlaneBlock;
+// Plans past the static workspace's size keep float32 operands where the
+// planes' padding would take more than this times their memory (square ones
+// below 20 x 20 or of 33 to 39: 200 000 of 2 x 2 need 318 MiB, and would need
+// 1.8 GiB for 46 instead of 103 ms a step).
+constexpr int64_t kPlaneMaxGrowth = 2;
 // The array of third parts takes 4 bytes per element of the corrected matrices
 // (less what the factored steps then share): up to this size.
 constexpr int64_t kThirdMaxBytes = (int64_t)1 << 31;
@@ -553,7 +558,7 @@ void plan_matrices(isoloco_plan_s* p) {
       const int64_t m = std::max(T.rows, T.cols), n = std::min(T.rows, T.cols);
       if (T.kind != ISOLOCO_KIND_ISO || (m >= 2 * n) != (pass == 0)) continue;
       ws_of[t] = ws;
-      ws += (padded(m) * padded(n) + 63) / 64 * 64;
+      ws += (padded(m) * n + 63) / 64 * 64;
     }
     if (pass == 0) p->n2d_tall = ws;
   }
@@ -1137,11 +1142,16 @@ isoloco_status isoloco_plan(const isoloco_tensor* layout, int32_t n_tensors, int
   isoloco_plan_s* p = nullptr;
   try {
     bool planes = o.precision == ISOLOCO_PREC_MIXED || o.precision == ISOLOCO_PREC_BF16X3;
-    int64_t iso = 0;
+    // elements of Delta, two iterates and two n x n matrices, without and with padding
+    int64_t plain = 0, padded = 0;
     for (int32_t i = 0; i < n_tensors; ++i)
       if (layout[i].kind == ISOLOCO_KIND_ISO) {
-        iso += layout[i].rows * layout[i].cols;
-        if (std::max(layout[i].rows, layout[i].cols) > kPlaneMaxRows) planes = false;
+        const int64_t m = std::max(layout[i].rows, layout[i].cols), n = std::min(layout[i].rows, layout[i].cols);
+        const int64_t mp = (m + kPlaneBlock - 1) / kPlaneBlock * kPlaneBlock;
+        const int64_t np = (n + kPlaneBlock - 1) / kPlaneBlock * kPlaneBlock;
+        plain += 3 * m * n + 2 * n * n;
+        padded += 3 * mp * n + 2 * np * np;
+        if (m > kPlaneMaxRows) planes = false;
       }
     p = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, planes);
     // On planes A M of the factored steps has no third part of A: a window that
@@ -1155,10 +1165,12 @@ isoloco_status isoloco_plan(const isoloco_tensor* layout, int32_t n_tensors, int
       delete q;
     }
     // The padding of many small matrices can take a plan past the static
-    // workspace that would fit without it: such a plan keeps float32 operands.
-    if (planes && p->total > ISOLOCO_STATIC_WORKSPACE_BYTES && 12 * iso <= (int64_t)ISOLOCO_STATIC_WORKSPACE_BYTES) {
+    // workspace that would fit without it, or multiply a workspace that is
+    // larger than that: such a plan keeps float32 operands.
+    const int64_t limit = ISOLOCO_STATIC_WORKSPACE_BYTES;
+    if (planes && p->total > ISOLOCO_STATIC_WORKSPACE_BYTES && (4 * plain <= limit || padded > kPlaneMaxGrowth * plain)) {
       isoloco_plan_s* q = build_plan(layout, n_tensors, n_elems, K, worker_dtype, o, false);
-      if (q->total <= ISOLOCO_STATIC_WORKSPACE_BYTES) std::swap(p, q);
+      if (q->total <= ISOLOCO_STATIC_WORKSPACE_BYTES || padded > kPlaneMaxGrowth * plain) std::swap(p, q);
       delete q;
     }
   } catch (...) {

@@ -9,11 +9,12 @@
 //
 // Layout ("planes"): a column of length L padded to a multiple of 32 is a run
 // of blocks of 32 consecutive elements, each block its 32 hi parts followed by
-// its 32 lo parts (128 bytes, a line of every cache).  Both dimensions are
-// padded to multiples of 32; the padding holds zeros, which every product keeps
-// at zero, so that odd sizes need no bounds checks inside the loops: a tile
-// that reaches past the padded matrix reads the last valid row or block again
-// (its outputs are not stored).
+// its 32 lo parts (128 bytes, a line of every cache).  The padding holds zeros,
+// which every product keeps at zero, so that odd sizes need no bounds checks
+// inside the loops.  The n x n matrices have their columns padded to a multiple
+// of 32 too, the iterates (for thin ones that would multiply the memory) only
+// their n: a tile that reaches past the columns or blocks there are reads the
+// last one again, and its outputs there are not stored (update) or zeroed (Gram).
 //
 // What bounds these products: at long K the power limit of the matrix cores
 // (update of one 4096 x 4096 matrix on 256 x 256 tiles: 68% MFMA busy at a clock
@@ -217,7 +218,9 @@ struct RowSlab {
   uint32_t vo[kLoads];
   uint64_t base;
   uint64_t step;
-  __device__ __forceinline__ void init(const uint16_t* tile, uint32_t col_bytes, int blocks_left) {
+  uint32_t col_b;
+  int cols;
+  __device__ __forceinline__ void init(const uint16_t* tile, uint32_t col_bytes, int blocks_left, int n) {
 #pragma unroll
     for (int q = 0; q < kLoads; ++q) {
       const int at = q * WAVES * 64 + threadIdx.x;  // 16-byte piece of the slab
@@ -228,12 +231,24 @@ struct RowSlab {
     }
     base = (uint64_t)tile;
     step = (uint64_t)kSlabK * col_bytes;
+    col_b = col_bytes;
+    cols = n;
   }
   __device__ __forceinline__ void load(uint32_t lds, int slab) const {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u32x4 r = tile_rsrc(base + step * (uint64_t)slab);
+    const int left = cols - slab * kSlabK;
+    if (left >= kSlabK) {
 #pragma unroll
-    for (int q = 0; q < kLoads; ++q) load_to_lds(lds + 1024u * (q * WAVES + wave), r, vo[q], 0);
+      for (int q = 0; q < kLoads; ++q) load_to_lds(lds + 1024u * (q * WAVES + wave), r, vo[q], 0);
+    } else {
+      // the last columns: past them the last one again (P's rows there are zero)
+#pragma unroll
+      for (int q = 0; q < kLoads; ++q) {
+        const int k = (q * WAVES * 64 + (int)threadIdx.x) / kPieces;
+        load_to_lds(lds + 1024u * (q * WAVES + wave), r, vo[q] - (uint32_t)max(k - left + 1, 0) * col_b, 0);
+      }
+    }
   }
   // 8 k values from k = kk + 8 (lane / 32) of row 32 blk + lane % 32, part p
   __device__ static __forceinline__ bf16x8 frag(const char* lds, int blk, int kk, int p) {
@@ -492,8 +507,8 @@ __global__ void __launch_bounds__(C::threads, 2) plane_gemm_kernel(PlaneArgs g) 
       akf.init(x + mi.ws_off + (int64_t)i0 * m + kb, m, n - i0, min(m, ke) - kb);
       bkf.init(y + mi.ws_off + (int64_t)j0 * m + kb, m, n - j0, min(m, ke) - kb);
     } else {
-      ak.init(planes(x + mi.ws_off + (int64_t)i0 * mp + kb), 4u * mp, np - i0);
-      bk.init(planes(y + mi.ws_off + (int64_t)j0 * mp + kb), 4u * mp, np - j0);
+      ak.init(planes(x + mi.ws_off + (int64_t)i0 * mp + kb), 4u * mp, n - i0);
+      bk.init(planes(y + mi.ws_off + (int64_t)j0 * mp + kb), 4u * mp, n - j0);
     }
   } else if constexpr (MODE == kPoly) {
     nslab = nb;
@@ -506,9 +521,9 @@ __global__ void __launch_bounds__(C::threads, 2) plane_gemm_kernel(PlaneArgs g) 
       if (g.first) scale = g.sc[task.mat].inv_fro;
       arf.init(g.xa + mi.ws_off + i0, m, m - i0, n);
     } else {
-      ar.init(planes(g.xa + mi.ws_off + i0), 4u * mp, (mp - i0) / 32);
+      ar.init(planes(g.xa + mi.ws_off + i0), 4u * mp, (mp - i0) / 32, n);
       if constexpr (X5)
-        ar3.init(g.third + 2 * mi.ws_off + (g.step & 1 ? (int64_t)mp * np : 0) + i0, 2u * mp, (mp - i0) / 32);
+        ar3.init(g.third + 2 * mi.ws_off + (g.step & 1 ? (int64_t)mp * n : 0) + i0, 2u * mp, (mp - i0) / 32, n);
     }
     bk.init(planes(g.sq + mi.sq_off + (int64_t)j0 * np), 4u * np, np - j0);
   }
@@ -679,9 +694,9 @@ __global__ void __launch_bounds__(C::threads, 2) plane_gemm_kernel(PlaneArgs g) 
       // (X_k's third parts are in the half of the matrix's span of k's parity)
       if (g.third_out)
         store_third<C>(acc, ws,
-                       reinterpret_cast<char*>(g.third_out + 2 * mi.ws_off + (g.step & 1 ? 0 : (int64_t)mp * np)),
-                       2 * (int64_t)mp, i0 / 32, mp / 32, j0, np);
-      store_columns<C>(acc, ws, reinterpret_cast<char*>(g.out + mi.ws_off), 4 * (int64_t)mp, i0 / 32, mp / 32, j0, np);
+                       reinterpret_cast<char*>(g.third_out + 2 * mi.ws_off + (g.step & 1 ? 0 : (int64_t)mp * n)),
+                       2 * (int64_t)mp, i0 / 32, mp / 32, j0, n);
+      store_columns<C>(acc, ws, reinterpret_cast<char*>(g.out + mi.ws_off), 4 * (int64_t)mp, i0 / 32, mp / 32, j0, n);
     }
     return;
   }
@@ -739,6 +754,20 @@ __global__ void __launch_bounds__(C::threads, 2) plane_gemm_kernel(PlaneArgs g) 
           }
         }
       __syncthreads();  // *last has been read: the staging may overwrite it
+    }
+    if (np != n) {
+      // past X's columns the operands were the last one again
+#pragma unroll
+      for (int a = 0; a < C::NA; ++a)
+#pragma unroll
+        for (int b = 0; b < C::NB; ++b) {
+          const int j = j0 + (wn * C::NB + b) * 32 + (lane & 31);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int i = i0 + (wm * C::NA + a) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+            if (i >= n || j >= n) acc[a][b][r] = 0.f;
+          }
+        }
     }
   } else {
 #pragma unroll

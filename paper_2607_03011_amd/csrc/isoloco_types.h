@@ -44,7 +44,8 @@ struct MatInfo {
   int64_t sq_off;    // element offset of this matrix's n x n buffers (Gram, polynomial)
   int64_t part_off;  // element offset of the split-K Gram partials (ksplit * n * n)
   int32_t m, n;      // tall shape
-  int32_t mp, np;    // plane layout: m and n padded to multiples of kPlaneBlock
+  int32_t mp, np;    // plane layout: m and n padded to multiples of kPlaneBlock (X: n columns of
+                     // mp; the n x n matrices: np columns of np)
   int32_t ksplit;    // number of K slices of the Gram product (1 = no split)
   int32_t kchunk;    // rows of X per K slice (multiple of kBK)
   int32_t vec;       // 1 if m and n are multiples of 4 (vector loads allowed)

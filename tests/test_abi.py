@@ -311,3 +311,23 @@ def test_part_products_are_the_modes(precision, parts):
         assert (p.update_parts_early, p.parts) == parts
         keeps = (layout, opts) in FLOAT32_OPERANDS[precision // 2:]
         assert p.planes == (precision in (0, 2) and not keeps)
+
+
+@pytest.mark.parametrize("rows, cols, count", [(4096, 8, 4000), (16, 4096, 200), (1001, 12, 300), (2, 2, 200000),
+                                               (16, 16, 20000), (80, 70, 2000), (33, 33, 20000), (65, 33, 10000)])
+@pytest.mark.parametrize("precision", [0, 2], ids=["mixed", "bf16x3"])
+def test_workspace_growth_is_bounded(rows, cols, count, precision):
+    """Thin and small matrices on the padded planes: past the static workspace's
+    size at most twice the memory of the plan that keeps float32 operands
+    (bf16x6), plus the third parts (as much again as one iterate at most)."""
+    layout = [(i * rows * cols, rows, cols, 0) for i in range(count)]
+    size = {}
+    for p in (precision, 3):
+        h = iso.isoloco_plan(layout, count * rows * cols, 2, 0, dict(precision=p))
+        size[p] = iso.isoloco_workspace_size(h)
+        iso.isoloco_plan_destroy(h)
+    print(rows, cols, count, size)
+    assert size[precision] <= max(iso.ISOLOCO_STATIC_WORKSPACE_BYTES, 2.7 * size[3])
+    if min(rows, cols) * 16 <= max(rows, cols):
+        # thin ones: the third parts are all that is added
+        assert size[precision] <= max(iso.ISOLOCO_STATIC_WORKSPACE_BYTES, 1.4 * size[3])

@@ -76,6 +76,8 @@ def test_block_and_tile_edges(iso, align, precision):
     ("256", (500, 628), 176), ("256 odd", (499, 633), 176),
     # tall: factored steps, and a split Gram
     ("128 tall", (120, 509), 170), ("split", (4500, 250), 10),
+    # thin, columns past n are not stored
+    ("thin", (1500, 8), 40), ("thin wide", (33, 2050), 20), ("thin split", (4611, 17), 12),
 ])
 def test_tile_shapes(iso, name, shape, count):
     print("case: %s, %d matrices of %d x %d" % (name, count, *shape), flush=True)
