@@ -494,14 +494,14 @@ void plan_plane_lists(isoloco_plan_s* p) {
     // 27 / 25 / -, of 48 (1008 / 288 of 128 / 256) - / 83 / 119, step with 96 of
     // 1024^2 (3456 / 960) 49.2 / 48.6 ms; update of 48 of 768^2 (1728 / 432)
     // - / 137 / 130, of one 4096^2 (1024 / 256) - / 354 / 309.
-    auto choose = [&](bool update) {
+    auto choose = [&](bool update, bool split) {
       int64_t tiles[3];
       for (int t : {kTileS, kTileM, kTileL}) {
         const int64_t S = kTileSide[t];
         tiles[t] = 0;
         for (int i : order) {
           const int64_t TN = (mats[i].np + S - 1) / S, TM = (mats[i].mp + S - 1) / S;
-          tiles[t] += update ? TM * TN : TN * (TN + 1) / 2 * mats[i].ksplit;
+          tiles[t] += update ? TM * TN : TN * (TN + 1) / 2 * (split ? mats[i].ksplit : 1);
         }
       }
       // (tiles on the diagonal compute more than they must: 1.25 allows for them)
@@ -515,8 +515,8 @@ void plan_plane_lists(isoloco_plan_s* p) {
       if (tiles[kTileM] >= (update ? 160 : 120) && 4 * tiles[kTileM] <= 1.6 * tiles[kTileS]) return (int)kTileM;
       return (int)kTileS;
     };
-    G.tile = choose(false);
-    U.tile = choose(true);
+    G.tile = choose(false, true);
+    U.tile = choose(true, false);
     std::stable_sort(order.begin(), order.end(),
                      [&](int a, int b) { return (int64_t)mats[a].kchunk > (int64_t)mats[b].kchunk; });
     const int S = kTileSide[G.tile], SU = kTileSide[U.tile];
@@ -531,11 +531,12 @@ void plan_plane_lists(isoloco_plan_s* p) {
         for (int b = 0; b < (mats[mi].np + SU - 1) / SU; ++b) U.tasks.push_back(Task{mi, a, b, 0});
     U.tasks = xcd_order(mats, U.tasks, false);
     if (!P) return;
-    // (the polynomial reads the blocks that the Gram's tiles left: one shape for both)
-    P->tile = G.tile;
+    // (the polynomial's tiles are its own: no K slices)
+    P->tile = choose(false, false);
+    const int SP = kTileSide[P->tile];
     for (int mi : order)
-      for (int a = 0; a < (mats[mi].np + S - 1) / S; ++a)
-        for (int b = a; b < (mats[mi].np + S - 1) / S; ++b) P->tasks.push_back(Task{mi, a, b, 0});
+      for (int a = 0; a < (mats[mi].np + SP - 1) / SP; ++a)
+        for (int b = a; b < (mats[mi].np + SP - 1) / SP; ++b) P->tasks.push_back(Task{mi, a, b, 0});
     P->tasks = xcd_order(mats, P->tasks, false);
   };
   build(p->mats, -1, p->gram_pl, &p->poly_pl, p->update_pl);

@@ -331,3 +331,22 @@ def test_workspace_growth_is_bounded(rows, cols, count, precision):
     if min(rows, cols) * 16 <= max(rows, cols):
         # thin ones: the third parts are all that is added
         assert size[precision] <= max(iso.ISOLOCO_STATIC_WORKSPACE_BYTES, 1.4 * size[3])
+
+
+def _products(shapes, opts=None):
+    layout, off = [], 0
+    for r, c in shapes:
+        layout.append((off, r, c, 0))
+        off += r * c
+    h = iso.isoloco_plan(layout, off, 2, 0, opts)
+    p = iso.isoloco_get_products(h)
+    iso.isoloco_plan_destroy(h)
+    return p
+
+
+@pytest.mark.parametrize("rows, cols", [(8192, 1024), (32000, 768)])
+def test_polynomial_tiles_do_not_count_k_slices(rows, cols):
+    """A tall matrix's Gram is cut into K slices, its polynomial is not: 36 or 21
+    tiles of 128 x 128 would leave most of the GPU idle."""
+    p = _products([(rows, cols)])
+    assert p.gram_tile[1] in (64, 128) and p.poly_tile[1] == 64
