@@ -479,21 +479,48 @@ void build_phases(const isoloco_options& o, const float (&bound)[3], std::vector
 
 // Side of the tiles of a plane product list: see plan_plane_lists.
 constexpr int kTileSide[3] = {64, 128, 256};
+// Compute units of the part the plans are made for (a plan is made without a device).
+constexpr int64_t kPlanCus = 256;
 
 // The work lists of the plane products: per list one tile shape, every matrix
 // covered by it (tiles may reach past a matrix).
 void plan_plane_lists(isoloco_plan_s* p) {
+  bool both[kSchedClasses] = {};
+  for (const MatInfo& mi : p->mats) both[mi.sched] = true;
+  const int sharing = p->opts.streams == 2 && both[kSchedSquare] && both[kSchedTall] ? 2 : 1;
   auto build = [&](const std::vector<MatInfo>& mats, int cls, PlaneListHost& G, PlaneListHost* P, PlaneListHost& U) {
     std::vector<int> order;
     for (size_t i = 0; i < mats.size(); ++i)
       if (cls < 0 || mats[i].sched == cls) order.push_back((int)i);
-    // The largest tiles that still fill the chip (each halves the operand
-    // traffic of the next smaller, but a launch of too few leaves CUs idle) and
-    // do not compute much more than the next smaller ones.  Measured (us per
-    // launch, 64 / 128 / 256): Gram of 8 matrices 768^2 (624 / 168 / 48 tiles)
-    // 27 / 25 / -, of 48 (1008 / 288 of 128 / 256) - / 83 / 119, step with 96 of
-    // 1024^2 (3456 / 960) 49.2 / 48.6 ms; update of 48 of 768^2 (1728 / 432)
-    // - / 137 / 130, of one 4096^2 (1024 / 256) - / 354 / 309.
+    // The tile shape by the rounds of workgroups that a launch takes: a CU holds
+    // three of 64-, two of 128- and one of 256-square tiles, each shape twice as
+    // cheap per output as the one before once the rounds are full.
+    //  - 64 while its tiles fit one round.  us per launch alone on the GPU, (tiles):
+    //    Gram of 6 matrices of 768^2 22 (468) against 27 with 128, of 8 26 (624)
+    //    against 28, of 10 34 (780) against 32; update of 5 27 (720) against 28, of
+    //    6 33 (864) against 29.  Two classes on two streams share the CUs: half a
+    //    round for the symmetric products (one d = 768 block, 312 and 234 tiles,
+    //    1204 against 1303 us a step with 128; two blocks, 624 and 468 tiles, 3864
+    //    against 3772), the updates as before (one block, 576: 1111 against 1203).
+    //  - 256 where its tiles fit one round that 128 exceeds (alone on the GPU), or
+    //    fill three quarters of more.  us a step: Gram and polynomial of one
+    //    4096^2 11158 (136) against 11754 with 128 (528), 25 of 768^2 2722 (150)
+    //    against 2696 (525), 28 2839 (168) against 2861 (588), 40 3869 (240) against
+    //    4134 (840); 20 2611 (120) against 2078 (420).  us per launch: Gram of 48
+    //    121 (288) against 87 (1008), of 96 of 1024^2 351 (960) against 356 (3456);
+    //    update of 20 67 (180) against 69 (720), 28 82 (252) against 89 (1008), 32
+    //    137 (288) against 109 (1152), 40 145 (360) against 132 (1440), 48 155 (432)
+    //    against 158 (1728), one 4200^2 626 (289) against 500 (1089), one 6144^2 1475
+    //    (576) against 1354 (2304), 32 of 1024^2 206 (512) against 224 (2048).
+    //    With two classes the other stream fills a part-empty round, and one round
+    //    of 256 leaves it no place: from one full round on for the updates (4 blocks
+    //    d = 612, f = 1637: 252 tiles 2110 against 2008 us a step; 2 blocks d = 1024:
+    //    264 tiles 3360 against 3405; one block d = 2048: 528 tiles 11320 against
+    //    11400), from two on for the symmetric products (tall Gram of 12 blocks
+    //    d = 768 and an embedding: 252 tiles 10361 against 10033, square 288 10114
+    //    against 10033; 24 blocks d = 1024: 960 and 780 tiles within 1%).
+    //  - where a shape computes much more past the matrices than the smaller one
+    //    (1.1 to 1.6 times, less the halves of diagonal tiles), the smaller one.
     auto choose = [&](bool update, bool split) {
       int64_t tiles[3];
       for (int t : {kTileS, kTileM, kTileL}) {
@@ -504,16 +531,13 @@ void plan_plane_lists(isoloco_plan_s* p) {
           tiles[t] += update ? TM * TN : TN * (TN + 1) / 2 * (split ? mats[i].ksplit : 1);
         }
       }
-      // (tiles on the diagonal compute more than they must: 1.25 allows for them)
-      if (tiles[kTileL] >= (update ? 256 : 512) && 4 * tiles[kTileL] <= (update ? 1.1 : 1.25) * tiles[kTileM])
-        return (int)kTileL;
-      // (a symmetric product whose 128 x 128 tiles just exceed two per CU would
-      // run a second round nearly empty: one round of 256 x 256 tiles, one
-      // matrix of 4096 x 4096 (136 against 528 tiles) 11.09 against 11.57 ms a step)
-      if (!update && tiles[kTileM] > 512 && tiles[kTileM] <= 600 && 4 * tiles[kTileL] <= 1.25 * tiles[kTileM])
-        return (int)kTileL;
-      if (tiles[kTileM] >= (update ? 160 : 120) && 4 * tiles[kTileM] <= 1.6 * tiles[kTileS]) return (int)kTileM;
-      return (int)kTileS;
+      const int64_t small = 3 * kPlanCus, medium = 2 * kPlanCus, large = kPlanCus;  // tiles of a round
+      if (tiles[kTileS] <= (update ? small : small / sharing)) return (int)kTileS;
+      const bool fits = sharing == 2              ? tiles[kTileL] >= (update ? large : 2 * large)
+                        : tiles[kTileL] < large ? tiles[kTileM] > medium
+                                                : 4 * tiles[kTileL] > 3 * ((tiles[kTileL] + large - 1) / large * large);
+      if (fits && 4 * tiles[kTileL] <= (update ? 1.1 : 1.25) * tiles[kTileM]) return (int)kTileL;
+      return (int)(4 * tiles[kTileM] <= 1.6 * tiles[kTileS] ? kTileM : kTileS);
     };
     G.tile = choose(false, true);
     U.tile = choose(true, false);
@@ -1007,17 +1031,18 @@ static isoloco_plan_s* build_plan(const isoloco_tensor* layout, int32_t n_tensor
   p->K = K;
   p->dtype = worker_dtype;
   p->planes = planes;
-  plan_matrices(p);
   if (o.streams == 0) {
     // Two streams fill each other's launch gaps and partial last waves,
     // which matter while launches are short; for large matrices the
     // concurrent products rather compete for the caches (paired
     // measurements: 109.5M parameters 2% faster, 341M 1%, 888M 4% slower).
     int64_t n2d = 0;
-    for (const MatInfo& mi : p->mats) n2d += (int64_t)mi.m * mi.n;
+    for (const isoloco_tensor& t : p->layout)
+      if (t.kind == ISOLOCO_KIND_ISO) n2d += t.rows * t.cols;
     o.streams = n2d <= kTwoStreamMaxElems ? 2 : 1;
   }
   p->opts = o;
+  plan_matrices(p);
   for (int c = 0; c < kSchedClasses; ++c)
     build_phases(o, c == kSchedTall ? o.phase_tall : o.phase_square, p->sched[c], p->phase_end[c],
                  p->phase_bound[c]);

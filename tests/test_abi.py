@@ -350,3 +350,37 @@ def test_polynomial_tiles_do_not_count_k_slices(rows, cols):
     tiles of 128 x 128 would leave most of the GPU idle."""
     p = _products([(rows, cols)])
     assert p.gram_tile[1] in (64, 128) and p.poly_tile[1] == 64
+
+
+TILES = [
+    # one class: 64 x 64 while its tiles fit one round of 768
+    ([(768, 768)] * 9, {}, 0, (64, 64, 128)), ([(768, 768)] * 10, {}, 0, (128, 128, 128)),
+    ([(768, 768)] * 5, {}, 0, (64, 64, 64)), ([(768, 768)] * 6, {}, 0, (64, 64, 128)),
+    # matrices no larger than a tile: it computes less
+    ([(40, 40)] * 2000, {}, 0, (64, 64, 64)),
+    # 256 x 256 where they fit one round of 256 that 128 x 128 exceeds (512)
+    ([(768, 768)] * 24, {}, 0, (128, 128, 256)), ([(768, 768)] * 25, {}, 0, (256, 256, 256)),
+    ([(768, 768)] * 42, {}, 0, (256, 256, 128)), ([(4096, 4096)], {}, 0, (256, 256, 256)),
+    ([(4200, 4200)], {}, 0, (256, 256, 128)),
+    # or fill three quarters of more rounds
+    ([(768, 768)] * 43, {}, 0, (128, 128, 256)), ([(768, 768)] * 48, {}, 0, (128, 128, 256)),
+    ([(6144, 6144)], {}, 0, (128, 128, 128)), ([(1024, 1024)] * 96, {}, 0, (256, 256, 256)),
+    # 640 = 5 x 128 = 2.5 x 256
+    ([(612, 612)] * 64, {}, 0, (128, 128, 128)),
+    # two classes on two streams: half a round of 64 x 64 for the symmetric
+    # products, full rounds of 256 x 256; on one stream as alone
+    ([(768, 768)] * 4 + [(2048, 768)] * 3, {}, 0, (64, 64, 64)),
+    ([(768, 768)] * 8 + [(2048, 768)] * 6, {}, 0, (128, 128, 128)),
+    ([(768, 768)] * 8 + [(2048, 768)] * 6, dict(streams=1), 0, (64, 64, 128)),
+    ([(768, 768)] * 25 + [(2048, 768)] * 9, {}, 0, (128, 128, 128)),
+    ([(768, 768)] * 25 + [(2048, 768)] * 11, {}, 1, (128, 128, 256)),
+    ([(1024, 1024)] * 96 + [(2816, 1024)] * 60, {}, 1, (256, 256, 256)),
+]
+
+
+@pytest.mark.parametrize("shapes, opts, cls, tiles", TILES, ids=lambda v: str(v)[:40].replace(" ", ""))
+def test_plane_tiles_at_the_rules_edges(shapes, opts, cls, tiles):
+    """The tile shapes either side of each line of the planner's rule."""
+    p = _products(shapes, opts)
+    assert p.planes == 1
+    assert (p.gram_tile[cls], p.poly_tile[cls], p.update_tile[cls]) == tiles
