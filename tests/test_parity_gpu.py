@@ -212,14 +212,19 @@ def test_split_k_gram(iso, precision):
     plan.close()
 
 
-@pytest.mark.parametrize("precision", [0, 2, 3], ids=["mixed", "bf16x3", "bf16x6"])
-def test_big_tiles_with_remainders(iso, precision):
-    """256 x 256 update tiles beside the 128 x 128 tiles they leave over, in
-    the modes whose updates take the 1024-thread kernel (mixed: bf16x5 and
-    bf16x3; bf16x3) and the 512-thread one (bf16x6)."""
+@pytest.mark.parametrize("precision, opts", [(0, {}), (2, {}), (3, {}), (0, dict(phase_tall=(0.1, 1e-4, 2e-8)))],
+                         ids=["mixed", "bf16x3", "bf16x6", "mixed_float32_operands"])
+def test_big_tiles_with_remainders(iso, precision, opts):
+    """256 x 256 update tiles beside the 128 x 128 tiles they leave over on float32
+    operands: in the mode of the 512-thread kernel (bf16x6), and in mixed (the
+    1024-thread one, bf16x5 and bf16x3) with a first bound that keeps float32
+    operands.  On planes these few matrices run 64 x 64 tiles."""
     from workload import custom_layout
     lay, n = custom_layout(BIG_MIXED, align=4)
-    _run_and_compare(iso, _cfg(lay, n, K=3), opts=dict(precision=precision))
+    plan = iso.IsoLoCoPlan(lay, n, 3, iso.ISOLOCO_F32, opts=dict(precision=precision, **opts))
+    assert plan.products().planes == (precision in (0, 2) and not opts)
+    _run_and_compare(iso, _cfg(lay, n, K=3), plan=plan)
+    plan.close()
 
 
 # The paper's variants of the step (Section 4.3's fast path, Appendix B's
@@ -318,10 +323,11 @@ def test_random_layouts(iso, seed):
 @pytest.mark.parametrize("seed", range(6))
 def test_random_big_tile_layouts(iso, seed):
     """Seeded random matrices whose sides are multiples of 4 (short sides 256
-    to about 800, long sides up to about 2800), so that the updates run on
-    256 x 256 tiles with 128 x 128 remainders of every kind (odd strips,
-    ragged edges), tall and square-ish, in the mixed, bf16x3 or bf16x6
-    products; every tensor against the oracle."""
+    to about 800, long sides up to about 2800), tall and square-ish: in bf16x6
+    the updates run on 256 x 256 tiles with 128 x 128 remainders of every kind
+    (odd strips, ragged edges), in mixed and bf16x3 on planes in 64 x 64 or
+    128 x 128 tiles that reach past the matrices; every tensor against the
+    oracle."""
     from workload import custom_layout
     rng = np.random.default_rng(2000 + seed)
     shapes = []

@@ -19,7 +19,7 @@ EDGES = [(1, 1), (5, 1), (1, 7), (33, 26), (31, 64), (40, 32), (66, 33), (81, 64
          (320, 255), (31, 300), (257, 700)]
 
 
-def _step(iso, shapes, align, opts=None, seed=0, static=False):
+def _step(iso, shapes, align, opts=None, seed=0, static=False, tiles=None):
     torch = pytest.importorskip("torch")
     from workload import custom_layout
     lay, n = custom_layout([(r, c, KIND_ISO) for r, c in shapes], align=align)
@@ -31,6 +31,9 @@ def _step(iso, shapes, align, opts=None, seed=0, static=False):
     theta = torch.zeros(n, device=dev)
     mom = torch.zeros(n, device=dev)
     plan = iso.IsoLoCoPlan(lay, n, 1, iso.ISOLOCO_F32, opts=opts, device=dev, workspace=not static)
+    if tiles:
+        p, cls = plan.products(), int(max(shapes[0]) >= 2 * min(shapes[0]))
+        assert (p.gram_tile[cls], p.poly_tile[cls], p.update_tile[cls]) == tiles
     (plan.aggregate_static if static else plan.aggregate)(theta, w, mom, 1.0, 0.7, 0.9)
     torch.cuda.synchronize()
     st = plan.stats()
@@ -69,20 +72,25 @@ def test_block_and_tile_edges(iso, align, precision):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("name, shape, count", [
+@pytest.mark.parametrize("precision", ["mixed", "bf16x3"])
+@pytest.mark.parametrize("name, shape, count, tiles", [
     # enough matrices for 128 x 128 and for 256 x 256 tiles, with and without
     # 16-byte aligned columns, tiles reaching past the matrix
-    ("128", (252, 316), 56), ("128 odd", (249, 313), 56),
-    ("256", (500, 628), 176), ("256 odd", (499, 633), 176),
+    ("128", (252, 316), 100, (128, 128, 128)), ("128 odd", (249, 313), 100, (128, 128, 128)),
+    ("256 symmetric", (500, 628), 60, (256, 256, 128)), ("256 symmetric odd", (499, 633), 60, (256, 256, 128)),
+    ("256 update", (500, 760), 40, (128, 128, 256)), ("256 update odd", (499, 757), 40, (128, 128, 256)),
     # tall: factored steps, and a split Gram
-    ("128 tall", (120, 509), 170), ("split", (4500, 250), 10),
+    ("128 tall", (120, 509), 300, (128, 128, 128)), ("256 tall", (233, 997), 64, (64, 64, 256)),
+    ("split", (4500, 250), 10, (64, 64, 256)), ("split 128", (4497, 250), 20, (128, 64, 128)),
     # thin, columns past n are not stored
-    ("thin", (1500, 8), 40), ("thin wide", (33, 2050), 20), ("thin split", (4611, 17), 12),
+    ("thin", (1500, 8), 40, (64, 64, 64)), ("thin wide", (33, 2050), 20, (64, 64, 64)),
+    ("thin split", (4611, 17), 12, (64, 64, 64)),
 ])
-def test_tile_shapes(iso, name, shape, count):
-    print("case: %s, %d matrices of %d x %d" % (name, count, *shape), flush=True)
+def test_tile_shapes(iso, name, shape, count, tiles, precision):
+    print("case: %s, %d matrices of %d x %d, %s" % (name, count, *shape, precision), flush=True)
     shapes = [shape] * count
-    lay, n, w, _, mom, st = _step(iso, shapes, 4, seed=count)
+    opts = {"precision": {"mixed": iso.ISOLOCO_PREC_MIXED, "bf16x3": iso.ISOLOCO_PREC_BF16X3}[precision]}
+    lay, n, w, _, mom, st = _step(iso, shapes, 4, opts, seed=count, tiles=tiles)
     _check(lay, n, w, mom, st, select=[0, count - 1])
     # every matrix of the launch: an orthogonal factor
     assert all(0 <= s.orth_resid <= 1e-4 for s in st)
