@@ -62,14 +62,19 @@ constexpr int kSlabK = 32;
 
 // 16 bytes per lane from memory to LDS: lane l's bytes land at lds_off + 16 l
 // (lds_off is wave-uniform).  No register receives the data; the loads count
-// in vmcnt like any other, and wait_slabs() below waits for them.  (m0 holds
-// the LDS address; nothing else in these kernels uses it.)
+// in vmcnt like any other, and wait_slabs() below waits for them.  m0 holds
+// the LDS address.  It is listed as clobbered, so that the compiler sets it again
+// for any use of its own (it has none here today); m0 is a reserved register,
+// of which the compiler warns.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(uint32_t lds_off, u32x4 rsrc, uint32_t voff, uint32_t soff) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(lds_off), "v"(voff), "s"(rsrc), "s"(soff)
-               : "memory");
+               : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // Wait until at most N of this wave's loads are outstanding and its LDS reads
 // have returned, then for every wave of the workgroup.
