@@ -51,14 +51,16 @@ def gemm_flops_per_step(layout, stats, check, precision, factored=(0, 0)):
     polynomial A A (n (n+1) n) and the update X P (2 m n^2).  A matrix that took
     s steps forms s + 1 Grams with the check (the last one measures Q^T Q), s
     polynomials and s updates.  A factored step of a tall matrix replaces its
-    Gram and update by the n x n products A M (2 n^3), M B and M P (symmetric,
-    n (n+1) n each).  Split-bf16 products issue one MFMA product per part
+    Gram and update by the n x n products A M, M B and M P: one of A M (on
+    float32 operands) and M P (on planes) whole (2 n^3), the others symmetric
+    (n (n+1) n each).  Split-bf16 products issue one MFMA product per part
     product (3, 5 or 6)."""
     early, late = PARTS[precision]
     first, end = factored
 
     def upd_parts(j):
-        # the update kernel's products of step j (the factored steps' A M too)
+        # the update kernel's products of step j (the factored steps' whole
+        # product too: on planes these steps start at 3 or later)
         return early if j < X6_STEPS else late
 
     f = 0
@@ -74,8 +76,8 @@ def gemm_flops_per_step(layout, stats, check, precision, factored=(0, 0)):
         k = factored_count(m, n, s, factored)
         nn = 2 * n ** 3 + 2 * n * (n + 1) * n
         f += s * (gram + poly + upd) + (gram if check else 0) + k * (nn - gram - upd)
-        # issued: the Grams, polynomials and the factored steps' M B and M P at
-        # the late part count; each update (and A M) at its step's
+        # issued: the Grams, polynomials and the factored steps' symmetric products
+        # at the late part count; each update (and the whole product) at its step's
         fm += ((s - k + (1 if check else 0)) * gram + s * poly + k * 2 * n * (n + 1) * n) * late
         for j in range(s):
             if k and first < j < end:
@@ -87,14 +89,15 @@ def gemm_flops_per_step(layout, stats, check, precision, factored=(0, 0)):
     return f, fm
 
 
-def gemm_bytes_per_step(layout, stats, factored=(0, 0)):
+def gemm_bytes_per_step(layout, stats, factored=(0, 0), third=False):
     """Algorithmic HBM bytes of the batched products of one outer step: per
     polar step of an m x n matrix (m >= n) the Gram reads X and writes A
     (4mn + 4n^2; a split-K Gram also writes and re-reads its slices), the
     polynomial reads A and writes P (8n^2), the update reads X and P and
     writes X' (8mn + 4n^2); s steps form s + 1 Grams.  A factored step reads
     two n x n operands and writes one in each of A M, M B and M P (36 n^2) in
-    place of its Gram and update."""
+    place of its Gram and update.  third: the third parts of X_1 and X_2 (2mn
+    bytes each) are written by one update and read by the next."""
     b = 0
     for (_, r, c, kind), st in zip(layout, stats):
         if kind != 0:
@@ -104,6 +107,8 @@ def gemm_bytes_per_step(layout, stats, factored=(0, 0)):
         k = factored_count(m, n, s, factored)
         b += (s + 1) * (4 * m * n + 4 * n * n) + s * (8 * n * n) + s * (8 * m * n + 4 * n * n)
         b += k * (36 * n * n - (4 * m * n + 4 * n * n) - (8 * m * n + 4 * n * n))
+        if third:
+            b += 4 * m * n * min(max(s - 1, 0), X6_STEPS - 1)
     return b
 
 
@@ -432,7 +437,8 @@ def main():
     sum_gbs = worker_sum_ceiling_gbs(torch, workers)
     fbytes = finish_bytes(cfg.layout)
     fin_gbs = fbytes / (per["finish_ms"] * 1e-3) / 1e9
-    gbytes = gemm_bytes_per_step(cfg.layout, st, factored)
+    products = plan.products()
+    gbytes = gemm_bytes_per_step(cfg.layout, st, factored, bool(products.third))
     mt = MEASURED_TRAFFIC
     measured = (mt["sources_sha256"] == sources_sha256() and mt["workload"] == args.workload
                 and mt["precision"] == args.precision and args.variant == "exact")
@@ -458,14 +464,15 @@ def main():
                    "polar_phase_ends": phase_ends, "tall_factored_steps": list(factored),
                    "alpha": cfg.alpha, "outer_lr": cfg.outer_lr, "mu": cfg.mu},
         "roofline": {"bound": "mfma", "kernel": "batched polar products (%s: Gram, polynomial, update)" %
-                     ("gemm_f32_kernel" if args.precision == "fp32" else
+                     ("plane_gemm_kernel" if products.planes else
+                      "gemm_f32_kernel" if args.precision == "fp32" else
                       "gemm_bf16_kernel, gemm_bf16_big_kernel" if args.precision == "bf16x6" else
-                      "plane_gemm_kernel"),
+                      "gemm_bf16_kernel, gemm_bf16_big16_kernel"),
                      "achieved": round(gemm_tfs, 3), "peak": peak, "unit": "TFLOP/s",
                      "frac": round(gemm_tfs / peak, 4),
                      "work": "the method's products as fp32 flops (symmetric Gram n(n+1)m, polynomial "
                              "n(n+1)n, update 2mn^2 per polar step; a factored step of a tall matrix: "
-                             "A M 2n^3, M B and M P n(n+1)n each) over the time some product runs",
+                             "of A M, M B and M P one 2n^3, two n(n+1)n each) over the time some product runs",
                      "traffic": mt["gemm_bytes_per_step"] if measured else None,
                      "traffic_unit": "HBM bytes per step over all product launches",
                      "traffic_source": ("stored: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on these sources "

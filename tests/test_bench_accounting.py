@@ -3,7 +3,8 @@ work, issued MFMA flops and bytes) against an enumeration of the products one
 outer step launches for each matrix: the polynomial iteration that replaces
 the SVD of Algorithm 2 (a Gram, a polynomial and an update per step, and the
 Gram of the final check), and the tall matrices' steps on n x n factors
-(B = A M, A_k = M B, P = p_k(A_k), M <- M P, then X = X_first M once), each
+(B = A M, A_k = M B, P = p_k(A_k), M <- M P, then X = X_first M once; on planes M P
+whole and the others as their upper halves, on float32 operands A M whole), each
 product with its shape, its symmetry and the step whose arithmetic it takes.
 The symmetric products count only their distinct output entries, enumerated
 one by one on small shapes."""
@@ -19,7 +20,12 @@ St = collections.namedtuple("St", "steps")
 _UPDATE_KERNEL = {"AM", "upd"}
 
 
-def _launches(m, n, s, window, check):
+def _planes(precision, window):
+    """Do the split products run on planes? (mixed: not with a window from step 1)"""
+    return precision == "bf16x3" or precision == "mixed" and not (window[1] and window[0] + 1 < bench.X6_STEPS)
+
+
+def _launches(m, n, s, window, check, planes):
     """(product, rows, cols, K, symmetric, step) of every product of one m x n
     matrix (m >= n) that took s polar steps."""
     first, end = window
@@ -31,10 +37,10 @@ def _launches(m, n, s, window, check):
         if fac and j == first:
             out.append(("poly", n, n, n, True, j))  # M = p_first(A)
             for q in range(first + 1, end):
-                out.append(("AM", n, n, n, False, q))  # B = A M
+                out.append(("AM half" if planes else "AM", n, n, n, planes, q))  # B = A M
                 out.append(("MB", n, n, n, True, q))  # A_q = M B (symmetric)
                 out.append(("poly", n, n, n, True, q))  # P = p_q(A_q)
-                out.append(("MP", n, n, n, True, q))  # M <- M P (symmetric)
+                out.append(("MP", n, n, n, not planes, q))  # M <- M P
             out.append(("upd", m, n, n, False, end - 1))  # X_end = X_first M
             j = end
         else:
@@ -72,17 +78,22 @@ def _bytes(product, rows, cols, k):
     return 4 * 3 * rows * cols  # A M, M B, M P: two n x n operands, one n x n result
 
 
-def _enumerated(layout, stats, check, precision, window):
+def _enumerated(layout, stats, check, precision, window, third=False):
     f = fm = b = 0
     for (_, r, c, kind), st in zip(layout, stats):
         if kind != 0:
             continue
         m, n = max(r, c), min(r, c)
-        for prod, rows, cols, k, sym, step in _launches(m, n, st.steps, window, check):
+        for prod, rows, cols, k, sym, step in _launches(m, n, st.steps, window, check, _planes(precision, window)):
             fl = 2 * _entries(rows, cols, sym) * k
             f += fl
             fm += fl * _parts(precision, prod, step)
             b += _bytes(prod, rows, cols, k)
+            if third and prod == "upd":
+                # the third parts of X_1 and X_2: read by the update of their step,
+                # written by the one before
+                b += 2 * rows * cols * (0 < step < bench.X6_STEPS)
+                b += 2 * rows * cols * (step + 1 < min(bench.X6_STEPS, st.steps))
     return f, fm, b
 
 
@@ -107,6 +118,9 @@ def test_small_shapes(precision, window, check):
         assert bench.gemm_flops_per_step(SMALL, st, check, precision, window) == (f, fm)
         if check:
             assert bench.gemm_bytes_per_step(SMALL, st, window) == b
+        if check and precision == "mixed" and (not window[1] or window[0] >= bench.X6_STEPS):
+            b = _enumerated(SMALL, st, check, precision, window, third=True)[2]
+            assert bench.gemm_bytes_per_step(SMALL, st, window, third=True) == b
 
 
 @pytest.mark.parametrize("precision", ["mixed", "bf16x3"])
