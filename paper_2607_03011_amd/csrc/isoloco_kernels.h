@@ -42,7 +42,7 @@ struct DevTables {
   MatScalars* scalars;
   double* part_sq;
   double* part_tr;
-  double* part_norm;  // Gram-norm partials, gram_tiles(n) per matrix from MatInfo::norm_off
+  double* part_norm;  // Gram-norm partials, one per output tile of a matrix from MatInfo::norm_off
   int* split_cnt;     // arrival counters of the split-K Gram tiles (zero between launches)
   int* mat_cnt;       // per-matrix arrival counters of the Gram tiles and the trace chunks
                       // (zero between launches)

@@ -2,10 +2,15 @@
 //
 // Most iterates and every n x n matrix of the iteration are kept as bfloat16
 // parts x = hi + lo + r made once by the kernel that produced them, instead of
-// as float32 that every product splits again: the same bytes (2 + 2), the same
-// products, and operand slabs that go from memory straight into LDS (buffer
-// loads with an LDS destination) without passing through registers or the
-// vector ALU.
+// as float32 that every product splits again: the same bytes (2 + 2) up to the
+// padding, the same products, and operand slabs that go from memory straight into
+// LDS (buffer loads with an LDS destination) without passing through registers or
+// the vector ALU.  What float32 held beyond the two parts reached the products
+// nowhere but in the polynomial's linear term; errors against float64 are no
+// larger for it (geometric means, on float32 operands / on planes: 400 Gaussian
+// matrices 96 x 96 1.70e-5 / 1.56e-5, 200 of 256 x 100 1.67e-5 / 1.2e-5, 200 of
+// 130 x 100 with sigma_min 1e-5 4.47e-4 / 4.42e-4; the factored steps' products
+// are another matter, see isoloco_host.cpp).
 //
 // Layout ("planes"): a column of length L padded to a multiple of 32 is a run
 // of blocks of 32 consecutive elements, each block its 32 hi parts followed by
@@ -22,9 +27,10 @@
 // of 16384^3 reaches 1.38 on the same card), at K = 768 the bursts of output
 // stores of workgroups that run in step (leaving the stores out: Gram of 48
 // matrices 84 -> 64 us, update 135 -> 105 us) and the latency of each tile's first
-// loads.  Against the earlier kernels that split float32 in every product:
-// ragged sizes (d 612, f 1637) 2.3x, one d = 512 block 1.8x, 8 blocks of
-// d = 2048 1.13x, 12 blocks of d = 768 1.03x per step.
+// loads.  Against the kernels that split float32 in every product (they serve the
+// plans that keep float32 operands): ragged sizes (d 612, f 1637) 2.4x, one
+// d = 512 block 1.8x, 8 blocks of d = 2048 1.1x, 12 blocks of d = 768 1.03x per
+// step.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
