@@ -318,10 +318,11 @@ typedef struct {
   float reduce_ms;  /* K-way reduction (+ Nesterov of the uncorrected tensors)     */
   float gram_ms;    /* batched Gram products X^T X, all steps (+ the check, and the
                        per-matrix decisions their last tiles take); with factored
-                       steps also their n x n products M B and M P                 */
+                       steps also their symmetric n x n products (M B and A M on
+                       planes, M B and M P on float32 operands)                    */
   float poly_ms;    /* batched polynomial products b A + c A^2, all steps          */
   float update_ms;  /* batched updates X <- X P, all steps (with factored steps
-                       also their n x n products A M)                              */
+                       also their whole n x n product, M P or A M)                 */
   float finish_ms;  /* fused Nesterov write-back of the corrected tensors          */
   float other_ms;   /* ||Delta||_F per matrix, the trace with sigma_bar, a phase end
                        without a check, the clip variants' composition             */
