@@ -384,3 +384,11 @@ def test_plane_tiles_at_the_rules_edges(shapes, opts, cls, tiles):
     p = _products(shapes, opts)
     assert p.planes == 1
     assert (p.gram_tile[cls], p.poly_tile[cls], p.update_tile[cls]) == tiles
+
+
+def test_get_products_rejects_null():
+    p = iso.isoloco_products()
+    assert iso._lib.isoloco_get_products(None, ctypes.byref(p)) == -1
+    h = iso.isoloco_plan(LAY, 8256, 4)
+    assert iso._lib.isoloco_get_products(h, None) == -1
+    iso.isoloco_plan_destroy(h)
